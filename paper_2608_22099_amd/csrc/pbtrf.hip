@@ -10,16 +10,16 @@
 //    A(j,j) is not > 0), scales column j by r = 1/d and applies
 //    A(i,c) -= L(i,j) L(c,j) to the trailing kd x kd triangle, one fused
 //    multiply-add per entry and step in the order of the steps, so the factor
-//    is bitwise that of the unblocked definition.  For kd <= 140 the columns
-//    j..j+kd+1 live in LDS (kd+2 column slots, so the column that enters is
-//    written while the step reads the others: one barrier per step); wider
-//    bands are updated in place in global memory.
+//    is bitwise that of the unblocked definition.  For kd <= 144 the window
+//    lives in LDS as 16 x 16 tiles (pbtrf_tile.hip); wider bands are updated
+//    in place in global memory, one column per barrier.
 //  * band_pbtrs: L y = b forward and L^T x = y backward, the dividing forward
 //    chain over L's columns and the backward chain over its rows.
 #include <algorithm>
 #include <climits>
 
 #include "getrs_ring.hpp"
+#include "pbtrf_tile.hpp"
 
 namespace bandlu {
 
@@ -28,83 +28,6 @@ int launch_chain(int mode, const RingParams &P, int64_t batch, hipStream_t s);
 namespace {
 
 constexpr int kCholThreads = 256;
-constexpr int kCholLdsMaxKd = 140;
-
-struct CholParams {
-    double *AB;
-    int32_t *info;
-    int64_t ldab, strideAB;
-    int n, kd;
-};
-
-// LDS window: column c at slot c % (kd+2), entry r (row c+r) at slot*(kd+1)+r
-__global__ __launch_bounds__(kCholThreads) void pbtrf_lds_kernel(CholParams P) {
-    extern __shared__ double win[];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int n = P.n, kd = P.kd, W = kd + 2, H = kd + 1;
-    double *AB = P.AB + int64_t(blockIdx.x) * P.strideAB;
-    const int64_t ldab = P.ldab;
-    auto at = [&](int c, int r) -> double & { return win[(c % W) * H + r]; };
-    // columns 0..kd enter
-    for (int q = tid; q < (kd + 1) * H; q += kCholThreads) {
-        const int c = q / H, r = q - c * H;
-        if (c < n) at(c, r) = c + r < n ? AB[r + int64_t(c) * ldab] : 0.0;
-    }
-    __syncthreads();
-    int info = 0;
-    // the columns that enter are read kPf steps ahead (a register ring), so
-    // that no step waits for its load
-    constexpr int kPf = 4;
-    auto ld_enter = [&](int ce) -> double {
-        return (ce < n && tid < H && ce + tid < n) ? AB[tid + int64_t(ce) * ldab] : 0.0;
-    };
-    double ring[kPf];
-#pragma unroll
-    for (int q = 0; q < kPf; ++q) ring[q] = ld_enter(kd + 1 + q);
-    for (int j0 = 0; j0 < n && !info; j0 += kPf)
-#pragma unroll
-    for (int q = 0; q < kPf; ++q) {
-        const int j = j0 + q;
-        if (j >= n) break;
-        const int kn = std::min(kd, n - 1 - j);
-        // the column that enters (j+kd+1), loaded kPf steps ago
-        const int ce = j + kd + 1;
-        const double enter = ring[q];
-        ring[q] = ld_enter(ce + kPf);
-        const double d0 = at(j, 0);
-        if (!(d0 > 0.0)) {
-            info = j + 1;
-            break;
-        }
-        const double d = __builtin_sqrt(d0);
-        const double r = 1.0 / d;
-        // trailing update A(j+b, j+a) for 1 <= a <= b <= kn: column j+a by
-        // wavefront, rows by lane (L(., j) formed where it is used)
-        const int sj = j % W;  // (one modulo per step; the other slots follow from it)
-        const double *cj = win + sj * H;
-        for (int a = 1 + wv; a <= kn; a += kCholThreads / 64) {
-            const int sa = sj + a >= W ? sj + a - W : sj + a;
-            double *ca = win + sa * H;
-            const double la = cj[a] * r;
-            for (int b = a + lane; b <= kn; b += 64)
-                ca[b - a] = __builtin_fma(-(cj[b] * r), la, ca[b - a]);
-        }
-        // column j is final
-        if (tid <= kn) AB[tid + int64_t(j) * ldab] = tid == 0 ? d : cj[tid] * r;
-        if (ce < n && tid < H) at(ce, tid) = enter;
-        __syncthreads();
-    }
-    if (info) {
-        // not positive definite at column info-1: the window's columns keep
-        // their updated values, as the unblocked algorithm leaves them
-        const int j = info - 1;
-        for (int q = tid; q < (kd + 1) * H; q += kCholThreads) {
-            const int c = j + q / H, r = q % H;
-            if (c < n && c + r < n && c <= j + kd) AB[r + int64_t(c) * ldab] = at(c, r);
-        }
-    }
-    if (tid == 0) P.info[blockIdx.x] = info;
-}
 
 __global__ __launch_bounds__(kCholThreads) void pbtrf_global_kernel(CholParams P) {
     const int tid = threadIdx.x;
@@ -158,20 +81,8 @@ int pbtrf(int64_t n, int64_t kd, double *dAB, int64_t ldab, int64_t strideAB, in
     P.strideAB = strideAB;
     P.n = (int)n;
     P.kd = (int)kd;
-    if (kd <= kCholLdsMaxKd) {
-        const size_t shm = size_t(kd + 2) * size_t(kd + 1) * sizeof(double);
-        if (shm > 64 * 1024) {
-            if (hipError_t e = hipFuncSetAttribute((const void *)pbtrf_lds_kernel,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   (int)shm);
-                e != hipSuccess)
-                return hip_fail(e, "band_pbtrf (LDS window size)");
-        }
-        hipLaunchKernelGGL(pbtrf_lds_kernel, dim3((unsigned)batch), dim3(kCholThreads), shm, s, P);
-    } else {
-        hipLaunchKernelGGL(pbtrf_global_kernel, dim3((unsigned)batch), dim3(kCholThreads), 0, s,
-                           P);
-    }
+    if (n > 0 && kd <= kCholTileMaxKd) return launch_pbtrf_tile(P, batch, s);
+    hipLaunchKernelGGL(pbtrf_global_kernel, dim3((unsigned)batch), dim3(kCholThreads), 0, s, P);
     BANDLU_CHECK_LAUNCH("band_pbtrf");
     return BANDLU_OK;
 }
