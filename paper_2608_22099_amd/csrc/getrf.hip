@@ -9,15 +9,17 @@
 //               with its diagonal pivot and checked against partial pivoting
 //               (getrf_diag.hpp); from the first column that fails, SPLIT
 //               factors the rest;
-//   SPLIT       1 <= kl <= 31 with the WINDOW limits: the window plus a
-//               second wavefront that runs the pivot decisions
-//               (getrf_split.hpp);
+//   SPLIT       1 <= kl <= 31 and 2kl+ku+1 <= 128: a register window in one
+//               wavefront per 64 columns plus a wavefront that runs the pivot
+//               decisions (getrf_split.hpp; also the m x n factorisation);
 //   WINDOW_G16  batched, kl <= 7 and 2kl+ku+1 <= 32, or any batch with
 //               1 <= kl <= 4 and 2kl+ku+1 <= 16: register window, 16 lanes
 //               per matrix, four matrices per wavefront;
-//   BLOCKED     kl <= 31 beyond the windows: panels of 32 columns factored in
-//               registers, trailing band updated by many workgroups with the
-//               unblocked rank-1 order (getrf_blocked.hip);
+//   BLOCKED     kl <= 31 beyond that, unblocked rank-1 order: the same kernel
+//               with blocks of 64 columns in up to seven wavefronts
+//               (1 <= kl, 2kl+ku+1 <= 448); past it panels of 32 columns
+//               factored in registers, the trailing band updated by many
+//               workgroups (getrf_blocked.hip);
 //   WIDE        32 <= kl <= 256 when the batch fits one launch of co-resident
 //               workgroups: one persistent launch, blocks of 32 columns kept
 //               in LDS, each panel factored by its block's owner and applied
@@ -49,17 +51,16 @@ WinKernel win_kernel_g64_c2_h1_8(int H);
 WinKernel win_kernel_g64_c2_h9_16(int H);
 WinKernel win_kernel_g16_c1_h1_8(int H);
 WinKernel win_kernel_g16_c2_h1_8(int H);
-WinKernel split_kernel_c1_h2_16(int H);
-WinKernel split_kernel_c1_h17_32(int H);
-WinKernel split_kernel_c2_h2_16(int H);
-
-// two-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32
+WinKernel split_kernel_h2_16(int H);
+WinKernel split_kernel_h17_24(int H);
+WinKernel split_kernel_h25_32(int H);
 WinKernel lean64_fwd_kernel_c1(int H);
 WinKernel lean64_fwd_kernel_c2(int H);
 
-WinKernel split_kernel(int CPL, int H) {
-    if (CPL == 1) return H <= 16 ? split_kernel_c1_h2_16(H) : split_kernel_c1_h17_32(H);
-    return split_kernel_c2_h2_16(H);
+// pivot-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32
+WinKernel split_kernel(int H) {
+    if (H <= 16) return split_kernel_h2_16(H);
+    return H <= 24 ? split_kernel_h17_24(H) : split_kernel_h25_32(H);
 }
 
 // diagonal-pivot kernel (getrf_diag.hpp) for 1 <= ku <= kDiagMaxKu
@@ -224,9 +225,47 @@ __global__ void zero_info_kernel(int32_t *info, int64_t batch) {
 }
 
 // Up to this kl the one-wavefront window kernel with wave-uniform pivots
-// (getrf_lean64.hpp) takes fewer cycles per column than the two-wavefront
+// (getrf_lean64.hpp) takes fewer cycles per column than the pivot-wavefront
 // kernel, for single matrices and after a failed diagonal-pivot check.
 constexpr int64_t kLeanMaxKl = 6;
+
+// The pivot-wavefront kernel (getrf_split.hpp): any kl in 1..31 with a window of
+// at most kSplitMaxU * 64 columns.  It is the faster one over all of that range:
+// 0.6-1.3 us per column against 3.2 (m x n, one workgroup in global memory) and
+// 5.4-5.6 (one launch per panel of 32 columns), and for 512 systems of n = 256,
+// kl = 31, ku = 60 0.34 ms against 5.1.  (A launch holds fewer than 2^32 threads.)
+unsigned split_threads(int64_t kl, int64_t ku) { return 64 * (1 + unsigned((2 * kl + ku + 64) / 64)); }
+
+bool split_fits(int64_t n, int64_t kl, int64_t ku, int64_t ldab, int64_t batch) {
+    return kl >= 1 && kl <= 31 && 2 * kl + ku + 1 <= 64 * kSplitMaxU &&
+           ldab * n * 8 <= kMaxBufferBytes && batch * split_threads(kl, ku) <= UINT32_MAX;
+}
+
+int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
+                 int64_t strideAB, int32_t *d_ipiv, int64_t strideP, int32_t *d_info,
+                 int64_t batch, hipStream_t s) {
+    WinParams W;
+    W.AB = dAB;
+    W.ipiv = d_ipiv;
+    W.info = d_info;
+    W.ldab = ldab;
+    W.strideAB = strideAB;
+    W.strideP = strideP;
+    W.n = (int)n;
+    W.m = (int)m;
+    W.ku = (int)ku;
+    W.batch = (int)batch;
+    W.kl = (int)kl;
+    W.resume = 0;
+    const WinKernel k = split_kernel((int)kl + 1);
+    if (!k) {
+        set_error("band_getrf: no pivot-wavefront kernel for kl = %lld", (long long)kl);
+        return BANDLU_ERR_UNSUPPORTED;
+    }
+    hipLaunchKernelGGL(k, dim3((unsigned)batch), dim3(split_threads(kl, ku)), 0, s, W);
+    BANDLU_CHECK_LAUNCH("band_getrf (pivot wavefront)");
+    return BANDLU_OK;
+}
 
 int select_variant(int64_t n, int64_t kl, int64_t ku, int64_t batch) {
     const int64_t need = 2 * kl + ku + 1;
@@ -238,9 +277,7 @@ int select_variant(int64_t n, int64_t kl, int64_t ku, int64_t batch) {
     if (diag_fits(n, kl, ku, need)) return BANDLU_GETRF_DIAG;
     if (kl >= 1 && kl <= kLeanMaxKl && need <= 128 && need * n * 8 <= kMaxBufferBytes)
         return BANDLU_GETRF_WINDOW;
-    if (kl >= 1 && kl <= 31 && (need <= 64 || (need <= 128 && kl <= 15)) &&
-        need * n * 8 <= kMaxBufferBytes)
-        return BANDLU_GETRF_SPLIT;
+    if (need <= 128 && split_fits(n, kl, ku, need, batch)) return BANDLU_GETRF_SPLIT;
     if (kl <= 31 && (need <= 64 || (need <= 128 && kl <= 15)) && need * n * 8 <= kMaxBufferBytes)
         return BANDLU_GETRF_WINDOW;
     // from kl = 32 on, applying a panel of 32 columns is a real dense product
@@ -265,8 +302,7 @@ bool variant_fits(int v, int64_t n, int64_t kl, int64_t ku, int64_t ldab, int64_
         return kl <= 31 && (need <= 64 || (need <= 128 && kl <= 15)) &&
                ldab * n * 8 <= kMaxBufferBytes;
     case BANDLU_GETRF_SPLIT:
-        return kl >= 1 && kl <= 31 && (need <= 64 || (need <= 128 && kl <= 15)) &&
-               ldab * n * 8 <= kMaxBufferBytes;
+        return need <= 128 && split_fits(n, kl, ku, ldab, batch);
     case BANDLU_GETRF_DIAG:
         return diag_fits(n, kl, ku, ldab);
     case BANDLU_GETRF_BLOCKED:
@@ -353,28 +389,8 @@ int launch_getrf(int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
         BANDLU_CHECK_LAUNCH("band_getrf (window)");
         return BANDLU_OK;
     }
-    if (v == BANDLU_GETRF_SPLIT) {
-        WinParams W;
-        W.AB = dAB;
-        W.ipiv = d_ipiv;
-        W.info = d_info;
-        W.ldab = ldab;
-        W.strideAB = strideAB;
-        W.strideP = strideP;
-        W.n = (int)n;
-        W.ku = (int)ku;
-        W.batch = (int)batch;
-        W.kl = (int)kl;
-        W.resume = 0;
-        const WinKernel k = split_kernel(need <= 64 ? 1 : 2, (int)kl + 1);
-        if (!k) {
-            set_error("band_getrf: no two-wavefront kernel for kl = %lld", (long long)kl);
-            return BANDLU_ERR_UNSUPPORTED;
-        }
-        hipLaunchKernelGGL(k, dim3((unsigned)batch), dim3(128), 0, s, W);
-        BANDLU_CHECK_LAUNCH("band_getrf (two wavefronts)");
-        return BANDLU_OK;
-    }
+    if (v == BANDLU_GETRF_SPLIT || (v == BANDLU_GETRF_BLOCKED && split_fits(n, kl, ku, ldab, batch)))
+        return launch_split(n, n, kl, ku, dAB, ldab, strideAB, d_ipiv, strideP, d_info, batch, s);
     if (v == BANDLU_GETRF_DIAG) {
         WinParams W;
         W.AB = dAB;
@@ -387,11 +403,12 @@ int launch_getrf(int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
         W.ku = (int)ku;
         W.batch = (int)batch;
         W.kl = (int)kl;
+        W.m = (int)n;
         W.resume = 0;
         const WinKernel k = diag_kernel((int)ku);
         // (the band fits 64 lanes: 2kl+ku+1 <= 64)
         const bool lean = kl <= kLeanMaxKl;
-        const WinKernel rest = lean ? win_kernel(64, 1, (int)kl + 1) : split_kernel(1, (int)kl + 1);
+        const WinKernel rest = lean ? win_kernel(64, 1, (int)kl + 1) : split_kernel((int)kl + 1);
         if (!k || !rest) {
             set_error("band_getrf: no diagonal-pivot kernel for kl = %lld, ku = %lld", (long long)kl,
                       (long long)ku);
@@ -624,8 +641,9 @@ extern "C" int band_getrf_batched_noalloc(int64_t n, int64_t kl, int64_t ku, dou
 }
 
 // ------------------------------------------------- rectangular m x n --
-// The band LU of an m x n band matrix (xGBTRF with m != n): the one-workgroup
-// kernel above with m rows, min(m, n) column steps and km = min(kl, m-1-j)
+// The band LU of an m x n band matrix (xGBTRF with m != n): the pivot-wavefront
+// kernel where it fits, else the one-workgroup kernel above, with m rows,
+// min(m, n) column steps and km = min(kl, m-1-j)
 // candidates per step; element (i, j), 0 <= i < m, at AB[kl+ku+i-j + j*ldab].
 namespace bandlu {
 namespace {
@@ -633,6 +651,9 @@ int getrf_mn(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t 
              int64_t strideAB, int32_t *d_ipiv, int64_t strideP, int32_t *d_info, int64_t batch,
              hipStream_t s) {
     if (batch == 0) return BANDLU_OK;
+    // the pivot-wavefront kernel wherever its registers hold the window
+    if (m > 0 && n > 0 && split_fits(n, kl, ku, ldab, batch))
+        return launch_split(m, n, kl, ku, dAB, ldab, strideAB, d_ipiv, strideP, d_info, batch, s);
     GenParams P;
     P.AB = dAB;
     P.ipiv = d_ipiv;

@@ -13,7 +13,7 @@
 // Every step checks that no candidate row outranks the diagonal before it
 // changes anything.  The first column j0 that fails ends the kernel: it writes
 // the band as it stands before step j0 and marks ipiv[n-1] = -(j0+1).  The
-// two-wavefront pivoting kernel then factors the trailing band from column j0
+// pivot-wavefront kernel then factors the trailing band from column j0
 // on as a problem of its own (getrf_split.hpp): steps 0..j0-1 interchanged
 // nothing, and the product-form L of xGBTRF never moves earlier multipliers.
 //

@@ -39,7 +39,8 @@ struct WinParams {
     int64_t ldab, strideAB, strideP;
     int n, ku, batch;
     int kl;      // read by the kernels that take kl at run time
-    int resume;  // two-wavefront and lean window kernels: continue where the diagonal-pivot kernel stopped
+    int m;       // rows (pivot-wavefront kernel: m x n; the others are square)
+    int resume;  // pivot-wavefront and lean window kernels: continue where the diagonal-pivot kernel stopped
     // lean window kernel with the forward solve: one right-hand side per
     // matrix, B + b * strideB (set only for that kernel)
     double *B = nullptr;
@@ -215,6 +216,9 @@ __global__ __launch_bounds__(64) void getrf_window_kernel(WinParams P) {
 constexpr int win_pf(int H) { return H * ((16 + H - 1) / H); }
 
 using WinKernel = void (*)(WinParams);
+
+// update waves of the pivot-wavefront kernel (eight waves in all, two per SIMD)
+constexpr int kSplitMaxU = 7;
 
 // Table of window kernels for H = LO..HI with fixed G and CPL.
 template <int G, int CPL, int LO, int HI>
