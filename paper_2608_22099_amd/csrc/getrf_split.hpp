@@ -64,16 +64,6 @@ __device__ __forceinline__ unsigned long long split_rotr(unsigned long long m, i
     return (m >> r) | ((m << 1) << (63 - r));
 }
 
-__device__ __forceinline__ unsigned split_wave_max(unsigned v) {
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));
-    const unsigned a = max((unsigned)__builtin_amdgcn_readlane((int)v, 0), (unsigned)__builtin_amdgcn_readlane((int)v, 16));
-    const unsigned b = max((unsigned)__builtin_amdgcn_readlane((int)v, 32), (unsigned)__builtin_amdgcn_readlane((int)v, 48));
-    return max(a, b);
-}
-
 // prefetch depth of a wave U: a multiple of H (so that every register slot
 // index is a compile-time constant), at least 16, and even for H <= 16 (so that
 // the parity of the LDS buffers is one too; beyond that the registers of twice
@@ -286,11 +276,11 @@ __global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinP
         const int toff = (L - u) & 63;
         const unsigned yhi = unsigned(__double_as_longlong(y) >> 32) & 0x7fffffffu;
         const unsigned khi = !inc ? 0u : (nan ? (toff == 0 ? 0x7ff00001u : 0u) : yhi);
-        unsigned long long hit = __ballot(khi == split_wave_max(khi)) & cand;
+        unsigned long long hit = __ballot(khi == wave_max_u32(khi)) & cand;
         if (__popcll(hit) > 1) {
             const bool tied = (hit >> L) & 1;
             const unsigned klo = (tied && !nan) ? unsigned(__double_as_longlong(y)) : 0u;
-            hit &= __ballot(klo == split_wave_max(klo));
+            hit &= __ballot(klo == wave_max_u32(klo));
         }
         const int p = __builtin_ctzll(split_rotr(hit, u));
         const int lp = (u + p) & 63;

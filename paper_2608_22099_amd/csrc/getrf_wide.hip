@@ -18,7 +18,8 @@
 // When all panels before it are applied the block is itself the next panel:
 // its owner factors it in place (first with every pivot on the diagonal,
 // verified column by column against partial pivoting; on the first failure
-// again with partial pivoting), publishes the panel's L (in the row order
+// again with partial pivoting, and from then on at once with it until a panel
+// has interchanged nothing), publishes the panel's L (in the row order
 // after the panel's interchanges, laid out for the matrix-core operands) in a
 // ring of G slots, and then writes the factors to the band (nothing on the
 // chain reads them there).  The owner of the next block applies the panel at
@@ -140,11 +141,16 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
     __shared__ double sL11[NB * LDW];
     __shared__ double sU[NB * LDU];
     __shared__ double sA[NB * (PR - NB)];  // the applied panel's -L21, column-major
-    __shared__ double sK[kWaves];
-    __shared__ int sI[kWaves];
-    __shared__ int s_perm[PR];
-    __shared__ int s_p[NB];
+    __shared__ int4 sKey[8];        // a step's candidates, by wave: |x| (high, low word), position
+    __shared__ double sRow[NB + 2];  // a step's pivot row, the reciprocal of the pivot at NB
+    __shared__ int s_p[NB];          // position of each step's pivot
     __shared__ int s_ok, s_ident, s_viol;
+    __shared__ int s_try;
+    if (t < 8) sKey[t] = make_int4(0, 0, INT_MAX, 0);
+    // whether the next panel of this workgroup is first tried without
+    // interchanges: until one has interchanged rows, and again after one that
+    // has not (either way factors a panel to the same bits)
+    if (t == 0) s_try = 1;
 
     // wait until panel k is published; false if the hand-off failed
     auto wait_panel = [&](int k) -> bool {
@@ -310,24 +316,24 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
             }
             __syncthreads();
             if (!s_ident) {
-                // the panel's interchanges as one gather of whole rows, eight
-                // columns at a time
+                // the panel's interchanges as one gather of whole rows, sixteen
+                // columns at a time (all 32 would spill)
                 const bool mv = t < Rw;
                 const double *from = W + prow(j0 + (mv ? sperm[t] : 0)) * LDW;
                 double *to = W + prow(j0 + (mv ? t : 0)) * LDW;
 #pragma unroll 1
-                for (int c0 = 0; c0 < NB; c0 += 8) {
-                    double v[8];
+                for (int c0 = 0; c0 < NB; c0 += 16) {
+                    double v[16];
                     if (mv) {
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) v[c] = from[c0 + c];
+                        for (int c = 0; c < 16; ++c) v[c] = from[c0 + c];
                     }
-                    __syncthreads();
+                    lds_barrier();
                     if (mv) {
 #pragma unroll
-                        for (int c = 0; c < 8; ++c) to[c0 + c] = v[c];
+                        for (int c = 0; c < 16; ++c) to[c0 + c] = v[c];
                     }
-                    __syncthreads();
+                    lds_barrier();
                 }
             }
             // U12 = L11^-1 * (rows 0..31) on wave 0, one lane per column, while
@@ -618,8 +624,9 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
                     AB[int64_t(j0 + c) * ldab + (kv + d)] = W[prow(j0 + w) * LDW + c];
             }
         };
-        bool spec_ok;
-        if (__builtin_amdgcn_readfirstlane(wv) == 0) {
+        bool spec_ok = false;
+        if (!__builtin_amdgcn_readfirstlane(s_try)) {
+        } else if (__builtin_amdgcn_readfirstlane(wv) == 0) {
             group_w0.template operator()<0, 8>();
             group_w0.template operator()<8, 8>();
             group_w0.template operator()<16, 8>();
@@ -643,120 +650,149 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
             if (spec_ok) commit_spec();
         }
         if (!spec_ok) {
-            // ---- partial pivoting, in the window in LDS: one thread per row,
-            // whole rows interchanged (so the window ends with L in its final
-            // row order, as the blocks it updates need it), four barriers per
-            // column step.  This path runs only for panels that interchange
-            // rows, and keeps few values in registers.
-            const int wvu = __builtin_amdgcn_readfirstlane(wv);
+            // ---- partial pivoting, one row per thread, its 32 entries in
+            // registers.  Rows do not move: each thread carries its row's position
+            // `pos` in the panel, which is all that an interchange changes.  In a
+            // step every wave looks for its best candidate (by lane maxima of the
+            // high words) and puts its key into LDS; after a barrier every wave
+            // picks the best of the five the same way, the wave that holds it
+            // hands its row and the reciprocal over, and after another barrier
+            // every wave applies it.
+            // Measured (n = 10000, kl = ku = 100, every panel interchanging; ms per
+            // factorisation): 30.8 with the rows in LDS, whole rows interchanged
+            // there and four barriers a step (and the attempt above before every
+            // panel); 13.1 with every wave's candidate row written before a single
+            // barrier (an LDS store of one lane takes as long as one of 64, and a
+            // hundred of them queue: 2300 cycles a step); 12.2 as it is (1800, a
+            // third of it fetching the unrolled steps); 15.8 as a loop over the
+            // steps with the entries moving one register down (each step then
+            // carries more columns than are left, and copies).
+            // (The row goes through pointers and indexes that the compiler cannot
+            // fold: their addresses are not kept in registers through the attempt
+            // above, which would spill.)
             const int myr = opaque_v(myr0);
             const bool own = myr >= 0 && myr < Rn;
-            double *const row1 = W + prow(j0 + max(myr, 0)) * LDW;
-            for (int i = t; i < PR; i += kThreads) s_perm[i] = i;
-            int pinfo = 0;
-            unsigned pz = 0;
-            __syncthreads();
-#pragma unroll 1
-            for (int jj = 0; jj < nbn; ++jj) {
-                const int col = j0 + jj;
-                const int km = min(kl, n - 1 - col);
-                const int tt = myr - jj;
-                const bool cand = own & (tt >= 0) & (tt <= km);
-                const double key = cand ? pivot_key(row1[jj], tt) : -2.0;
-                const double wmax = wave_max_d(key);
-                // rows are in lane order inside a wave: the lowest lane with
-                // the largest key is the first such row
-                const unsigned long long hit = __ballot(key == wmax);
-                const int f = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-                const int frow = __builtin_amdgcn_readlane(myr, f);
-                if (lane == 0) {
-                    sK[wvu] = wmax;
-                    sI[wvu] = wmax > -2.0 ? frow : INT_MAX;
-                }
-                __syncthreads();
-                double bk = sK[0];
-                int bi = sI[0];
+            const int wvu = __builtin_amdgcn_readfirstlane(wv);
+            const int lane = opaque_v(t & 63);
+            double *const row = sRow + opaque_v(0);
+            int4 *const key = sKey + opaque_v(0);
+            double y[NB];
 #pragma unroll
-                for (int w2 = 1; w2 < kWaves; ++w2) {
-                    const double kw = sK[w2];
-                    const int iw = sI[w2];
-                    const bool bt = key_better(kw, iw, bk, bi);
-                    bk = bt ? kw : bk;
-                    bi = bt ? iw : bi;
-                }
-                const int p = bi - jj;  // uniform
-                double *const prow_j = W + prow(col) * LDW;
-                double *const prow_p = W + prow(col + p) * LDW;
-                const double piv = prow_p[jj];
-                if (t == 0) {
-                    ipiv[col] = col + p + 1;
-                    s_p[jj] = p;
-                }
-                const bool elim = piv != 0.0;
-                if (!elim) {
-                    pz |= 1u << jj;
-                    if (pinfo == 0) pinfo = col + 1;
-                }
-                __syncthreads();
-                if (elim && p != 0) {
-                    if (t < NB) {
-                        const double a0 = prow_j[t];
-                        prow_j[t] = prow_p[t];
-                        prow_p[t] = a0;
-                    } else if (t == NB) {
-                        const int a0 = s_perm[jj];
-                        s_perm[jj] = s_perm[jj + p];
-                        s_perm[jj + p] = a0;
+            for (int c = 0; c < NB; ++c) y[c] = own ? W[prow(j0 + max(myr, 0)) * LDW + c] : 0.0;
+            int pos = myr;
+            int pinfo = 0;
+            unsigned pz = 0;     // columns whose pivot is zero
+            bool moved = false;  // uniform: the panel has interchanged rows
+            // (ties are rare: one row at a time, on scalars, to keep the unrolled
+            // steps small)
+            auto settle = [&](unsigned long long hit, int lo, int at) __attribute__((always_inline)) -> int {
+                int f = __builtin_ctzll(hit);
+                unsigned bl = (unsigned)__builtin_amdgcn_readlane(lo, f);
+                int bp = __builtin_amdgcn_readlane(at, f);
+#pragma unroll 1
+                for (hit &= hit - 1; hit != 0; hit &= hit - 1) {
+                    const int g = __builtin_ctzll(hit);
+                    const unsigned gl = (unsigned)__builtin_amdgcn_readlane(lo, g);
+                    const int gp = __builtin_amdgcn_readlane(at, g);
+                    if (gl > bl || (gl == bl && gp < bp)) {
+                        f = g;
+                        bl = gl;
+                        bp = gp;
                     }
                 }
-                __syncthreads();
-                if (elim && own && tt >= 1 && tt <= km) {
-                    const double l = fabs(piv) >= DBL_MIN ? row1[jj] * (1.0 / piv) : row1[jj] / piv;
-                    row1[jj] = l;
-#pragma unroll 1
-                    for (int c = jj + 1; c < NB; ++c) row1[c] = __builtin_fma(-l, prow_j[c], row1[c]);
+                return f;
+            };
+            auto step = [&]<int S>() __attribute__((always_inline)) {
+                if (S >= nbn) return;
+                step_fence();
+                const int km = min(kl, n - 1 - (j0 + S));
+                const bool cand = own & (pos >= S) & (pos - S <= km);
+                // (formed beside the search, not after it)
+                double rcp0 = 1.0 / y[S];
+                const bool nan = __builtin_isnan(y[S]);
+                const unsigned yhi = unsigned(__double_as_longlong(y[S]) >> 32) & 0x7fffffffu;
+                const unsigned ylo = nan ? 0u : unsigned(__double_as_longlong(y[S]));
+                const unsigned khi = nan ? (pos == S ? 0x7ff00001u : 0u) : yhi;
+                const unsigned wmax = wave_max_u32(cand ? khi : 0u);
+                const unsigned long long hit = __ballot(khi == wmax) & __ballot(cand);
+                asm volatile("" : "+v"(rcp0));
+                const int f = (hit & (hit - 1)) == 0 ? __builtin_ctzll(hit | (1ull << 63))
+                                                     : settle(hit, (int)ylo, pos);
+                // (a wave with no candidate loses to every row)
+                if (lane == f) key[wvu] = make_int4((int)wmax, (int)ylo, hit == 0 ? INT_MAX : pos, 0);
+                lds_barrier();
+                // the best of the waves' candidates: lane w of each group of
+                // eight looks at wave w's (places 5..7 never win)
+                const int4 ck = key[lane & 7];
+                const unsigned best = group8_max_u32((unsigned)ck.x);
+                const unsigned who = unsigned(__ballot((unsigned)ck.x == best)) & 0xffu;
+                const int ww = (who & (who - 1)) == 0 ? __builtin_ctz(who) : settle(who, ck.y, ck.z);
+                const int p = __builtin_amdgcn_readlane(ck.z, ww);
+                if (wvu == ww) {
+                    if (lane == f) {
+                        row[NB] = rcp0;
+#pragma unroll
+                        for (int c = S; c < NB; ++c) {
+                            row[c] = y[c];
+                            step_fence();  // (a paired store would first copy both into adjacent registers)
+                        }
+                        s_p[S] = p;
+                    }
                 }
-                __syncthreads();
-            }
-            // the band: U rows and the multipliers in product form (each in
-            // the row its data row had when its column was eliminated, found
-            // by replaying the interchanges from the data row's first place)
-            if (own) {
-                int pos = s_perm[myr];
-#pragma unroll 1
-                for (int jj = 0; jj < nbn; ++jj) {
-                    const int col = j0 + jj;
-                    const int p = s_p[jj];
-                    if (!((pz >> jj) & 1u) && p != 0)
-                        pos = pos == jj ? jj + p : (pos == jj + p ? jj : pos);
-                    const int km = min(kl, n - 1 - col);
-                    if (pos > jj && pos - jj <= km)
-                        AB[int64_t(col) * ldab + (kv + pos - jj)] = row1[jj];
-                }
-#pragma unroll 1
-                for (int c = myr; c < nbn; ++c)
-                    if (myr - c >= -kv) AB[int64_t(j0 + c) * ldab + (kv + myr - c)] = row1[c];
-            }
-            // the panel's L in its final row order for the blocks it updates
-            if (myr >= 0) {
-                gperm[myr] = s_perm[myr];
-                if (myr < NB) {
-#pragma unroll 1
-                    for (int s2 = 0; s2 < NB; ++s2)
-                        gL11[s2 * NB + myr] = (own && s2 < myr && !((pz >> s2) & 1u)) ? row1[s2] : 0.0;
+                lds_barrier();
+                const double piv = uniform_d(row[S]);
+                const double rcp = row[NB];
+                double u[NB];
+#pragma unroll
+                for (int c = S + 1; c < NB; ++c) u[c] = row[c];
+                if (piv != 0.0) {
+                    moved |= p != S;
+                    pos = pos == S ? p : (pos == p ? S : pos);
+                    if (own & (pos > S) & (pos - S <= km)) {
+                        double l = y[S] * rcp;
+                        if (!(fabs(piv) >= DBL_MIN)) {
+                            l = y[S] / piv;
+                            asm volatile("" : "+v"(l));  // (stays a branch)
+                        }
+                        y[S] = l;
+#pragma unroll
+                        for (int c = S + 1; c < NB; ++c) y[c] = __builtin_fma(-l, u[c], y[c]);
+                    }
                 } else {
-#pragma unroll 1
-                    for (int s2 = 0; s2 < NB; ++s2)
-                        gNL[s2 * (PR - NB) + myr - NB] =
-                            (own && s2 < nbn && !((pz >> s2) & 1u)) ? -row1[s2] : 0.0;
+                    pz |= 1u << S;
+                    if (pinfo == 0) pinfo = j0 + S + 1;
                 }
+            };
+            [&]<int... S>(std::integer_sequence<int, S...>) __attribute__((always_inline)) {
+                (step.template operator()<S>(), ...);
+            }(std::make_integer_sequence<int, NB>{});
+            // the panel's L in the row order after the interchanges (mostly
+            // consecutive rows) for the blocks it updates: L11 for rows 0..31,
+            // -L21 below; zero-pivot columns, columns past the matrix and rows
+            // outside it contribute zeros
+            if (myr >= 0) {
+                const unsigned zm = __builtin_amdgcn_readfirstlane(pz);
+                gperm[pos] = myr;
+#pragma unroll
+                for (int sc = 0; sc < NB; ++sc) {
+                    const bool on = own && sc < nbn && !((zm >> sc) & 1u);
+                    if (pos < NB)
+                        gL11[sc * NB + pos] = (on && sc < pos) ? y[sc] : 0.0;
+                    else
+                        gNL[sc * (PR - NB) + (pos - NB)] = on ? -y[sc] : 0.0;
+                }
+                // (the rows back to the window, from where the band is written
+                // after the hand-over)
+                double *const back = W + prow(j0 + myr) * LDW;
+#pragma unroll
+                for (int c = 0; c < NB; ++c) back[c] = y[c];
             }
             if (t == 0) {
-                gperm[PR] = 0;
+                gperm[PR] = moved ? 0 : 1;
                 if (pinfo != 0 && *info == 0) *info = pinfo;
             }
+            if (t == 0) s_try = !moved;
         }
-        static_assert(NB + (kWaves - 1) * 64 == PR, "one thread per window row");
         // publish the panel
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __syncthreads();
@@ -764,8 +800,24 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
         __syncthreads();
         if (spec_ok) {
             commit_band();
-            __syncthreads();  // the window is loaded again next
+        } else {
+            // entry c of a row lies where the row was after step c's interchange:
+            // its multiplier until it is the pivot row, its U entry from then on
+            const int myr = opaque_v(myr0);
+            const bool own = myr >= 0 && myr < Rn;
+            const int mp = prow(j0 + max(myr, 0)) * LDW;
+            if (t < nbn) ipiv[j0 + t] = j0 + s_p[t] + 1;
+            int q = myr;
+#pragma unroll 4
+            for (int c = 0; c < nbn; ++c) {
+                const int p = __builtin_amdgcn_readfirstlane(s_p[c]);
+                q = q == c ? p : (q == p ? c : q);
+                if (own && q - c <= kl && q - c >= -kv)
+                    AB[int64_t(j0 + c) * ldab + (kv + q - c)] = W[mp + c];
+            }
         }
+        __syncthreads();  // the window is loaded again next
+        static_assert(NB + (kWaves - 1) * 64 == PR, "one thread per window row");
     }
 }
 

@@ -48,18 +48,6 @@ __device__ __forceinline__ unsigned long long rotr64(unsigned long long m, int r
     return (m >> r) | ((m << 1) << (63 - r));
 }
 
-// Maximum over the 64 lanes of a 32-bit unsigned key, uniform: one DPP max per
-// level inside rows of 16 lanes, then the four row maxima.
-__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false));
-    v = max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false));
-    const unsigned a = max((unsigned)__builtin_amdgcn_readlane((int)v, 0), (unsigned)__builtin_amdgcn_readlane((int)v, 16));
-    const unsigned b = max((unsigned)__builtin_amdgcn_readlane((int)v, 32), (unsigned)__builtin_amdgcn_readlane((int)v, 48));
-    return max(a, b);
-}
-
 __device__ __forceinline__ bool in_mask(unsigned long long m) {
     return __builtin_amdgcn_inverse_ballot_w64(m);
 }
