@@ -352,30 +352,67 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
 #pragma unroll
                 for (int u = 0; u < kPieces / (kThreads - 64); ++u) dst[i0 + u * (kThreads - 64)] = v[u];
             }
-            if (wv == 0 && lane < NB) {
+            if (wv == 0) {
+                // In two halves of 16 rows, the first one's share of the second on
+                // the matrix cores (in the order of the steps, as below): a step by
+                // lanes reads its factors from LDS at about 20 cycles each, so the
+                // 256 that the product takes over are half of the substitution.
+                // Measured (dominant rows): n = 32768, kl = ku = 256 27.48 -> 27.10
+                // ms, n = 10000, kl = ku = 100 8.31 -> 8.10, though 184 more bytes
+                // a lane spill around the update below.
                 // rows j0..j0+31 are 32 consecutive physical rows (288 and
                 // every window start are multiples of 32)
-                double *const col = W + opaque(prow(j0) * LDW) + lane;
+                double *const top = W + opaque(prow(j0) * LDW);
                 // (a base the compiler cannot fold: every load below is then
                 // this register plus an immediate offset, instead of an address
                 // register of its own hoisted out of the loops)
                 const double *const Lm = sL11 + opaque_v(0);
-                double y[NB];
+                auto half = [&]<int R0>() __attribute__((always_inline)) {
+                    double *const col = top + opaque_v(lane);
+                    double y[16];
 #pragma unroll
-                for (int r = 0; r < NB; ++r) y[r] = col[r * LDW];
+                    for (int r = 0; r < 16; ++r) y[r] = col[(R0 + r) * LDW];
 #pragma unroll
-                for (int s = 0; s < NB - 1; ++s) {
-                    // one step's 31-s factor loads issued together, then used
-                    step_fence();
-                    double lv[NB];
+                    for (int s = 0; s < 15; ++s) {
+                        // one step's 15-s factor loads issued together, then used
+                        step_fence();
+                        double lv[16];
 #pragma unroll
-                    for (int r = s + 1; r < NB; ++r) lv[r] = Lm[r * LDW + s];
-                    step_fence();
+                        for (int r = s + 1; r < 16; ++r) lv[r] = Lm[(R0 + r) * LDW + R0 + s];
+                        step_fence();
 #pragma unroll
-                    for (int r = s + 1; r < NB; ++r) y[r] = __builtin_fma(-lv[r], y[s], y[r]);
+                        for (int r = s + 1; r < 16; ++r) y[r] = __builtin_fma(-lv[r], y[s], y[r]);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) col[(R0 + r) * LDW] = y[r];
+                };
+                if (lane < NB) half.template operator()<0>();
+                __builtin_amdgcn_wave_barrier();
+                step_fence();
+                {
+                    const int ml = opaque_v(lane), ln = ml & 15, lk = ml >> 4;
+                    double *const at = top + lk * LDW + ln;
+                    const double *const la = Lm + (16 + ln) * LDW + lk;
+                    v4d acc[2];
+#pragma unroll
+                    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) acc[ct][q] = at[(16 + 4 * q) * LDW + 16 * ct];
+#pragma unroll
+                    for (int kb = 0; kb < 4; ++kb) {
+                        const double a = -la[4 * kb];
+#pragma unroll
+                        for (int ct = 0; ct < 2; ++ct)
+                            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, at[4 * kb * LDW + 16 * ct], acc[ct], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int ct = 0; ct < 2; ++ct)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) at[(16 + 4 * q) * LDW + 16 * ct] = acc[ct][q];
                 }
-#pragma unroll
-                for (int r = 0; r < NB; ++r) col[r * LDW] = y[r];
+                __builtin_amdgcn_wave_barrier();
+                step_fence();
+                if (lane < NB) half.template operator()<16>();
             }
             __syncthreads();
             // rows 32..Rw-1 += (-L21) * U12 on the matrix cores, wave g (1..4)
