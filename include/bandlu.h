@@ -218,7 +218,10 @@ int band_getrs_batched(int64_t n, int64_t kl, int64_t ku, int64_t nrhs, const do
                                     /* (kl <= 7: the pivot decided on scalars)  */
 #define BANDLU_GETRF_WINDOW_G16 2   /* register window, 16 lanes per matrix     */
 #define BANDLU_GETRF_GENERIC 3      /* unblocked, one workgroup per matrix      */
-#define BANDLU_GETRF_BLOCKED 4      /* blocks of columns, exact rank-1 updates  */
+#define BANDLU_GETRF_BLOCKED 4      /* blocked, exact rank-1 trailing updates;  */
+                                    /* unless forced, SPLIT's kernel with up to */
+                                    /* seven update wavefronts where 1 <= kl    */
+                                    /* and 2kl+ku+1 <= 448                      */
 #define BANDLU_GETRF_BLOCKED_MFMA 5 /* blocked, fp64 MFMA trailing update       */
 #define BANDLU_GETRF_SPLIT 6        /* register window + a pivot wavefront      */
 #define BANDLU_GETRF_DIAG 7         /* diagonal pivots verified per column; the */

@@ -15,11 +15,11 @@
 //   WINDOW_G16  batched, kl <= 7 and 2kl+ku+1 <= 32, or any batch with
 //               1 <= kl <= 4 and 2kl+ku+1 <= 16: register window, 16 lanes
 //               per matrix, four matrices per wavefront;
-//   BLOCKED     kl <= 31 beyond that, unblocked rank-1 order: the same kernel
-//               with blocks of 64 columns in up to seven wavefronts
-//               (1 <= kl, 2kl+ku+1 <= 448); past it panels of 32 columns
-//               factored in registers, the trailing band updated by many
-//               workgroups (getrf_blocked.hip);
+//   BLOCKED     kl <= 31 beyond that, unblocked rank-1 order: panels of 32
+//               columns factored in registers, the trailing band updated by
+//               many workgroups (getrf_blocked.hip).  Where the caller does
+//               not name a variant and 1 <= kl, 2kl+ku+1 <= 448, the SPLIT
+//               kernel with up to seven update wavefronts does the same;
 //   WIDE        32 <= kl <= 256 when the batch fits one launch of co-resident
 //               workgroups: one persistent launch, blocks of 32 columns kept
 //               in LDS, each panel factored by its block's owner and applied
@@ -389,7 +389,9 @@ int launch_getrf(int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
         BANDLU_CHECK_LAUNCH("band_getrf (window)");
         return BANDLU_OK;
     }
-    if (v == BANDLU_GETRF_SPLIT || (v == BANDLU_GETRF_BLOCKED && split_fits(n, kl, ku, ldab, batch)))
+    // (a caller who names BLOCKED gets the panel kernel)
+    if (v == BANDLU_GETRF_SPLIT ||
+        (variant == 0 && v == BANDLU_GETRF_BLOCKED && split_fits(n, kl, ku, ldab, batch)))
         return launch_split(n, n, kl, ku, dAB, ldab, strideAB, d_ipiv, strideP, d_info, batch, s);
     if (v == BANDLU_GETRF_DIAG) {
         WinParams W;

@@ -1,7 +1,8 @@
 // Blocked banded LU with partial pivoting for wide bands (Sec. III-A's
 // specialised algorithm f(N) when kl+ku is large): xGBTRF in panels of NB = 32
-// columns, one launch per panel; for windows that the pivot-wavefront kernel's
-// registers do not hold (kl = 0, 2kl+ku+1 > 448, or a band of 2 GiB).
+// columns, one launch per panel; by default for windows that the
+// pivot-wavefront kernel's registers do not hold (kl = 0, 2kl+ku+1 > 448, or a
+// band of 2 GiB), and for any kl <= 256 where the caller names it.
 //
 // Launch k covers the band columns that panel k-1 can still change (up to
 // j0 + NB - 1 + kl + ku) in blocks of 32 columns, one workgroup per block and
