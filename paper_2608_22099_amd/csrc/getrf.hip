@@ -54,13 +54,19 @@ WinKernel win_kernel_g16_c2_h1_8(int H);
 WinKernel split_kernel_h2_16(int H);
 WinKernel split_kernel_h17_24(int H);
 WinKernel split_kernel_h25_32(int H);
+WinKernel split_one_h2_16(int H);
+WinKernel split_one_h17_24(int H);
+WinKernel split_one_h25_32(int H);
+WinKernel split_two_h8_16(int H);
 WinKernel lean64_fwd_kernel_c1(int H);
 WinKernel lean64_fwd_kernel_c2(int H);
 
-// pivot-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32
-WinKernel split_kernel(int H) {
-    if (H <= 16) return split_kernel_h2_16(H);
-    return H <= 24 ? split_kernel_h17_24(H) : split_kernel_h25_32(H);
+// pivot-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32: one update
+// wavefront, or any number
+WinKernel split_kernel(int H, bool one) {
+    if (H <= 16) return one ? split_one_h2_16(H) : split_kernel_h2_16(H);
+    if (H <= 24) return one ? split_one_h17_24(H) : split_kernel_h17_24(H);
+    return one ? split_one_h25_32(H) : split_kernel_h25_32(H);
 }
 
 // diagonal-pivot kernel (getrf_diag.hpp) for 1 <= ku <= kDiagMaxKu
@@ -230,15 +236,47 @@ __global__ void zero_info_kernel(int32_t *info, int64_t batch) {
 constexpr int64_t kLeanMaxKl = 6;
 
 // The pivot-wavefront kernel (getrf_split.hpp): any kl in 1..31 with a window of
-// at most kSplitMaxU * 64 columns.  It is the faster one over all of that range:
-// 0.6-1.3 us per column against 3.2 (m x n, one workgroup in global memory) and
-// 5.4-5.6 (one launch per panel of 32 columns), and for 512 systems of n = 256,
-// kl = 31, ku = 60 0.34 ms against 5.1.  (A launch holds fewer than 2^32 threads.)
+// at most kSplitMaxU * 64 columns.  Against the kernels it replaced there: 0.6-1.3
+// us per column for 3.2 (m x n, one workgroup in global memory) and 5.4-5.6 (one
+// launch per panel of 32 columns), and for 512 systems of n = 256, kl = 31, ku = 60
+// 0.34 ms for 5.1.  (A launch holds fewer than 2^32 threads.)
 unsigned split_threads(int64_t kl, int64_t ku) { return 64 * (1 + unsigned((2 * kl + ku + 64) / 64)); }
 
 bool split_fits(int64_t n, int64_t kl, int64_t ku, int64_t ldab, int64_t batch) {
     return kl >= 1 && kl <= 31 && 2 * kl + ku + 1 <= 64 * kSplitMaxU &&
            ldab * n * 8 <= kMaxBufferBytes && batch * split_threads(kl, ku) <= UINT32_MAX;
+}
+
+// Windows of 65..128 columns, 7 <= kl <= 15: one update wavefront with two columns
+// per lane instead of two wavefronts.  A single matrix is faster with two (kl =
+// 12, ku = 90: 651 ns per column for 864), and so are batches of up to two
+// matrices per CU and those of more rounds than one.  In between, where all
+// matrices are resident at once and three wavefronts a matrix crowd the SIMDs, two
+// a matrix are faster: up to four matrices per CU while the second half of the
+// window is nearly empty (1024 systems of n = 256, 65 columns, kl = 7: 239 us for
+// 270; kl = 10: 249 for 352), barely above two otherwise (640 systems, 100
+// columns, kl = 10: 217 for 239).  For kl = 13 and 14 the two wavefronts' registers
+// leave room for two matrices per CU only (4096 systems, 65 columns, kl = 14: 1214
+// us for 1664); from about 80 columns on that is no loss (100 columns: 2041 for
+// 1725), as fewer matrices share the cache.
+bool split_two_columns(int64_t kl, int64_t need, int64_t batch) {
+    if (need <= 64 || need > 128 || kl < 7 || kl > 15 || batch <= 512) return false;
+    if (need > 80) return batch <= 704;
+    return batch <= 1024 || kl == 13 || kl == 14;
+}
+
+// Dynamic LDS that keeps a fifth workgroup off a CU.  A step touches one line per
+// column of the window, so that more than four matrices of 57 to 128 columns evict
+// each other's lines from the CU's cache; where the registers would let five or
+// more be resident, large batches are faster with four (8192 systems of n = 256,
+// kl = 9, 80 columns: 2634 us for 3118, 2807 with two columns per lane; of n =
+// 200, kl = 16, 64 columns, dominant: 1265 for 1488).  One wavefront U and at most
+// 56 columns: all that fit (kl = 16, 40 columns: 1044 us for 1386).
+unsigned split_lds(int64_t kl, int64_t need, int64_t batch) {
+    constexpr unsigned four = 38000;  // (each kernel has 1552 bytes of its own)
+    if (batch <= 1024 || need > 128) return 0;
+    if (need > 64) return four;
+    return need > 56 && kl >= 16 && kl <= 19 ? four : 0;
 }
 
 int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
@@ -257,12 +295,15 @@ int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int6
     W.batch = (int)batch;
     W.kl = (int)kl;
     W.resume = 0;
-    const WinKernel k = split_kernel((int)kl + 1);
+    const int64_t need = 2 * kl + ku + 1;
+    const bool two = split_two_columns(kl, need, batch);
+    const WinKernel k = two ? split_two_h8_16((int)kl + 1) : split_kernel((int)kl + 1, need <= 64);
     if (!k) {
         set_error("band_getrf: no pivot-wavefront kernel for kl = %lld", (long long)kl);
         return BANDLU_ERR_UNSUPPORTED;
     }
-    hipLaunchKernelGGL(k, dim3((unsigned)batch), dim3(split_threads(kl, ku)), 0, s, W);
+    hipLaunchKernelGGL(k, dim3((unsigned)batch), dim3(two ? 128 : split_threads(kl, ku)),
+                       two ? 0 : split_lds(kl, need, batch), s, W);
     BANDLU_CHECK_LAUNCH("band_getrf (pivot wavefront)");
     return BANDLU_OK;
 }
@@ -410,7 +451,7 @@ int launch_getrf(int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
         const WinKernel k = diag_kernel((int)ku);
         // (the band fits 64 lanes: 2kl+ku+1 <= 64)
         const bool lean = kl <= kLeanMaxKl;
-        const WinKernel rest = lean ? win_kernel(64, 1, (int)kl + 1) : split_kernel((int)kl + 1);
+        const WinKernel rest = lean ? win_kernel(64, 1, (int)kl + 1) : split_kernel((int)kl + 1, true);
         if (!k || !rest) {
             set_error("band_getrf: no diagonal-pivot kernel for kl = %lld, ku = %lld", (long long)kl,
                       (long long)ku);

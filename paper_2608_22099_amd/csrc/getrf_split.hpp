@@ -17,7 +17,8 @@
 //     multipliers to the waves U;
 //   waves U (updates) run one step behind with the band window in registers:
 //     column c in lane (c mod M) mod 64 of wave (c mod M) / 64 (M = 64 NU for
-//     NU waves, M >= 2kl+ku+1), row r in slot r mod H (H = kl + 1).  At its step
+//     NU waves, M >= 2kl+ku+1; one wave may hold M = 128, two columns per
+//     lane), row r in slot r mod H (H = kl + 1).  At its step
 //     j a wave applies the interchange and the rank-1 update of step j-1 to its
 //     columns, stores row j-1 of U, refills the freed slot with the row that
 //     enters, and the wave that holds them stores the multipliers of column
@@ -37,8 +38,8 @@
 // the kernel that each of them replaced): n = 4096, kl = ku = 31: 5430 -> 1029
 // (one launch per panel of 32 columns); kl = 20, ku = 200: 5600 -> 943;
 // kl = 31, ku = 385: 5600 -> 1328; 8192, kl = 12, ku = 90: 864 -> 651 (both
-// blocks of 64 columns in one wave); kl = ku = 16: 727 -> 702; 9216 x 8192 with
-// kl = ku = 16: 3207 -> 704 (the window in global memory).
+// blocks of 64 columns in one wave); kl = ku = 16: 727 -> 672; 9216 x 8192 with
+// kl = ku = 16: 3207 -> 663 (the window in global memory).
 #pragma once
 
 #include <cfloat>
@@ -97,17 +98,23 @@ __device__ __forceinline__ void split_swap(double (&a)[H], int p) {
     else group.template operator()<25>();
 }
 
-template <int H>
-__global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinParams P) {
+// CPL: columns per lane; NU: waves U (0: as many as the launch has).  One wave U
+// has kernels of its own: with M known, single matrices of kl = 9..31 took 2-12 %
+// less (kl = 16, n = 5000: 3525 -> 3305 us random, 2930 -> 2645 dominant).
+// CPL = 2 (one wave U for 65..128 columns) runs batches whose matrices all fit
+// the chip at once: see split_two_columns() in getrf.hip.
+template <int H, int CPL, int NU>
+__global__ __launch_bounds__(CPL == 1 ? 64 * (1 + kSplitMaxU) : 128) void getrf_split_kernel(WinParams P) {
     constexpr int PF = split_pf(H);
     static_assert(H >= 2 && H <= 32, "window of 2..32 rows");
     static_assert(PF % H == 0 && PF + 1 <= 64, "prefetch depth: a multiple of H below 64");
+    static_assert(CPL == 1 || NU == 1, "several columns per lane in one wave U");
     constexpr int kl = H - 1;
     const int tid = threadIdx.x;
     const int L = tid & 63;
     const int64_t b = blockIdx.x;  // one matrix per workgroup
     const int ku = P.ku, kv = kl + P.ku, ldab = int(P.ldab);
-    const int M = int(blockDim.x) - 64;  // columns that the waves U hold
+    const int M = NU ? 64 * CPL * NU : int(blockDim.x) - 64;  // columns that the waves U hold
     int n = P.n, m = P.m;
     double *ABb = P.AB + b * P.strideAB;
     int32_t *ipb = P.ipiv + b * P.strideP;
@@ -139,31 +146,40 @@ __global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinP
 
     if (tid >= 64) {
         // ----------------------------------------------------------- waves U --
-        const int w0 = (__builtin_amdgcn_readfirstlane(tid) >> 6) * 64 - 64;  // first column of this wave
-        // column that this lane holds at step x: the first c >= x with
-        // c mod M = w0 + L; xm = x mod M
-        auto colof = [&](int x, int xm) -> int {
+        // first column of this wave
+        const int w0 = NU == 1 ? 0 : (__builtin_amdgcn_readfirstlane(tid) >> 6) * 64 - 64;
+        // column that this lane holds in sub-slot s at step x: the first c >= x
+        // with c mod M = w0 + 64 s + L; xm = x mod M
+        auto colof = [&](int s, int x, int xm) -> int {
+            if (NU == 1) return x + ((L + 64 * s - x) & (64 * CPL - 1));
             const int d = w0 + L - xm;
             return x + (d < 0 ? d + M : d);
         };
-        double a[H];
-        double pf[PF];
+        double a[CPL][H];
+        double pf[CPL][PF];
 #pragma unroll
-        for (int r = 0; r < H; ++r)
-            a[r] = buf_ld(ab, foff(r, r < H - 1 ? colof(r - H + 1, M + r - H + 1) : colof(0, 0)));
+        for (int s = 0; s < CPL; ++s) {
 #pragma unroll
-        for (int k = 0; k < PF; ++k) pf[k] = buf_ld(ab, foff(k + H, colof(k + 1, k + 1)));
+            for (int r = 0; r < H; ++r)
+                a[s][r] = buf_ld(ab, foff(r, r < H - 1 ? colof(s, r - H + 1, M + r - H + 1) : colof(s, 0, 0)));
+#pragma unroll
+            for (int k = 0; k < PF; ++k) pf[s][k] = buf_ld(ab, foff(k + H, colof(s, k + 1, k + 1)));
+        }
         int ju = 0;
         // column 1, rows 0..kl (no step applied yet) for wave P's step 1: it
         // sits in lane 1 of the first wave, slots 0..kl
         if (tid == 64 + 1) {
 #pragma unroll
-            for (int t = 0; t < H; ++t) s_col[0][t] = a[t];
+            for (int t = 0; t < H; ++t) s_col[0][t] = a[0][t];
         }
         lds_barrier();
+        // (with one wave U they stay in vector registers: one instruction less)
+        auto uni = [](int v) __attribute__((always_inline)) -> int {
+            return NU == 1 ? v : __builtin_amdgcn_readfirstlane(v);
+        };
         bool live = true;
         int odd = 0;  // parity of the block's first step (0 where PF is even)
-        int jm = 0;   // jj mod M
+        int jm = 0;   // jj mod M (several waves U)
         auto ustep = [&]<int U>(int jj) __attribute__((always_inline)) {
             constexpr int S0 = U % H;
             if (!live) return;
@@ -173,14 +189,21 @@ __global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinP
             }
             const int par = PF & 1 ? (U & 1) ^ odd : U & 1;  // jj & 1
             // ---- step jj as decided by wave P
-            const int pv = __builtin_amdgcn_readfirstlane(s_pv[par][0]);
-            const int nz = __builtin_amdgcn_readfirstlane(s_pv[par][1]);
-            const int c = colof(jj, jm);
+            const int pv = uni(s_pv[par][0]);
+            const int nz = uni(s_pv[par][1]);
+            int c[CPL];
+#pragma unroll
+            for (int s = 0; s < CPL; ++s) c[s] = colof(s, jj, jm);
             if (nz) {
                 ju = max(ju, min(jj + ku + pv, n - 1));
                 if (pv != 0) {
                     // interchange rows jj and jj+pv in columns jj..ju
-                    if (c <= ju) split_swap<H, S0>(a, pv);
+#pragma unroll
+                    for (int s = 0; s < CPL; ++s)
+                        if (c[s] <= ju) {
+                            if constexpr (CPL == 2 || (NU == 1 && H <= 9)) win_swap<H, S0>(a[s], pv);
+                            else split_swap<H, S0>(a[s], pv);
+                        }
                 }
                 double lm[H];
 #pragma unroll
@@ -188,37 +211,46 @@ __global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinP
                 // rank-1 update of columns jj+1..ju, under an exec mask (the empty
                 // volatile asm keeps the block a branch: as selects it would cost
                 // two more instructions per entry)
-                if (c > jj && c <= ju) {
-                    const double uu = a[S0];
 #pragma unroll
-                    for (int t = 1; t < H; ++t)
-                        a[(S0 + t) % H] = __builtin_fma(-lm[t], uu, a[(S0 + t) % H]);
-                    asm volatile("" ::: "memory");
+                for (int s = 0; s < CPL; ++s) {
+                    if (c[s] > jj && c[s] <= ju) {
+                        const double uu = a[s][S0];
+#pragma unroll
+                        for (int t = 1; t < H; ++t)
+                            a[s][(S0 + t) % H] = __builtin_fma(-lm[t], uu, a[s][(S0 + t) % H]);
+                        asm volatile("" ::: "memory");
+                    }
                 }
             }
             // ---- multipliers of column jj (as wave P formed them; for a zero pivot
             // the column as it is) into the band, by the wave that holds the
             // column: no store can overtake a load of an original entry of it
-            if (unsigned(jm - w0) < 64u) {
+            if (NU == 1 || unsigned(jm - w0) < 64u) {
                 const int kmj = min(kl, m - 1 - jj);
                 const double lv = s_l[par][L & 31];
                 buf_st(ab, (L >= 1 && L <= kmj) ? uint32_t(jj * ldab + kv + L) * 8u : kOutside, lv);
             }
             // ---- row jj of U leaves the window (columns jj..jj+kv; a retired
             // column has c >= jj+M-H+1 > jj+kv), row jj+H enters
-            {
-                const bool ok = c < n && c <= jj + kv;
-                buf_st(ab, ok ? uint32_t(c * ldab + kv + jj - c) * 8u : kOutside, a[S0]);
-                a[S0] = pf[U];
-                pf[U] = buf_ld(ab, foff(jj + PF + H, c > jj + PF ? c : c + M));
+#pragma unroll
+            for (int s = 0; s < CPL; ++s) {
+                const bool ok = c[s] < n && c[s] <= jj + kv;
+                buf_st(ab, ok ? uint32_t(c[s] * ldab + kv + jj - c[s]) * 8u : kOutside, a[s][S0]);
+                a[s][S0] = pf[s][U];
+                pf[s][U] = buf_ld(ab, foff(jj + PF + H, c[s] > jj + PF ? c[s] : c[s] + M));
             }
             // ---- column jj+2, rows jj+1..jj+1+kl (through step jj), for wave P
-            jm = jm + 1 == M ? 0 : jm + 1;
+            if (NU != 1) jm = jm + 1 == M ? 0 : jm + 1;
             if (jj + 2 < steps) {
-                const int wc = jm + 1 == M ? 0 : jm + 1;
-                if (L == wc - w0) {
+                const int wc = NU == 1 ? (jj + 2) & (M - 1) : (jm + 1 == M ? 0 : jm + 1) - w0;
+                if (L == (CPL == 1 ? wc : wc & 63)) {
+                    if (CPL == 1 || wc < 64) {
 #pragma unroll
-                    for (int t = 0; t < H; ++t) s_col[par ^ 1][t] = a[(S0 + 1 + t) % H];
+                        for (int t = 0; t < H; ++t) s_col[par ^ 1][t] = a[0][(S0 + 1 + t) % H];
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < H; ++t) s_col[par ^ 1][t] = a[CPL - 1][(S0 + 1 + t) % H];
+                    }
                 }
             }
             if (jj + 1 < steps) lds_barrier();
@@ -322,16 +354,21 @@ __global__ __launch_bounds__(64 * (1 + kSplitMaxU)) void getrf_split_kernel(WinP
 }
 
 // the kernels for H = LO..HI
-template <int LO, int HI>
+template <int LO, int HI, int CPL, int NU>
 struct SplitRange {
     template <int... Is>
     static constexpr auto make(std::integer_sequence<int, Is...>) {
-        return std::array<WinKernel, HI - LO + 1>{{&getrf_split_kernel<LO + Is>...}};
+        return std::array<WinKernel, HI - LO + 1>{{&getrf_split_kernel<LO + Is, CPL, NU>...}};
     }
 };
 
+// any number of waves U; one wave U; one wave U with two columns per lane
 WinKernel split_kernel_h2_16(int H);
 WinKernel split_kernel_h17_24(int H);
 WinKernel split_kernel_h25_32(int H);
+WinKernel split_one_h2_16(int H);
+WinKernel split_one_h17_24(int H);
+WinKernel split_one_h25_32(int H);
+WinKernel split_two_h8_16(int H);
 
 }  // namespace bandlu

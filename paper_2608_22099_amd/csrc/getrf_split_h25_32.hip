@@ -1,11 +1,12 @@
-// Banded LU with a pivot wavefront (getrf_split.hpp) instantiated for
-// kl + 1 = 25..32 (one file per range keeps compiles parallel).
+// Banded LU with a pivot wavefront (getrf_split.hpp), any number of update
+// wavefronts, instantiated for kl + 1 = 25..32 (one file per range keeps
+// compiles parallel).
 #include "getrf_split.hpp"
 
 namespace bandlu {
 
 WinKernel split_kernel_h25_32(int H) {
-    static constexpr auto table = SplitRange<25, 32>::make(std::make_integer_sequence<int, 32 - 25 + 1>{});
+    static constexpr auto table = SplitRange<25, 32, 1, 0>::make(std::make_integer_sequence<int, 32 - 25 + 1>{});
     return (H >= 25 && H <= 32) ? table[H - 25] : nullptr;
 }
 

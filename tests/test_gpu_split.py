@@ -100,3 +100,29 @@ def test_batched():
         ipo, info_o, _ = oracle.gbtrf(AB[b], kl, ku)
         assert np.array_equal(ipiv.cpu().numpy()[b], ipo) and int(info.cpu()[b]) == info_o
         assert same(ABg.cpu().numpy()[b], AB[b])
+
+
+@pytest.mark.parametrize("batch,kl,need", [(513, 7, 65), (1024, 12, 80), (1030, 14, 66), (1025, 13, 80),
+                                           (704, 15, 81), (600, 9, 128), (705, 11, 81), (1025, 9, 65),
+                                           (1025, 15, 128), (1025, 16, 57), (1030, 19, 64)])
+def test_batch_rules(batch, kl, need):
+    """Batches at the edges of the rules for two columns per lane and for the
+    number of resident workgroups; a few matrices of each batch, and the same
+    for a band of fewer rows than columns."""
+    ku = need - 2 * kl - 1
+    print(f"batch={batch} kl={kl} need={need}", flush=True)
+    for m, n in ((need + 70, need + 70), (need + 40, need + 70)):
+        base = [band(m, n, kl, ku, 1300 + b, b % 2 * 2.0 * (kl + ku)) for b in range(5)]
+        AB = np.stack([base[b % 5] for b in range(batch)])
+        ABg = gpu(AB)
+        if m == n:
+            ipiv, info = bandlu.band_getrf_batched(ABg, kl, ku, variant="split")
+        else:
+            ipiv, info = bandlu.band_getrf_mn_batched(ABg, m, kl, ku)
+        torch.cuda.synchronize()
+        ABg, ipiv, info = ABg.cpu().numpy(), ipiv.cpu().numpy(), info.cpu().numpy()
+        for b in range(5):
+            ipo, info_o, _ = oracle.gbtrf_mn(base[b], m, kl, ku)
+            assert np.all(ipiv[b::5] == ipo) and np.all(info[b::5] == info_o)
+            for k in range(b, batch, 5):
+                assert same(ABg[k], base[b])
