@@ -73,17 +73,24 @@ __global__ void sym_check_kernel(const double *A, int64_t n, int64_t lda, int64_
 
 int pbtrf(int64_t n, int64_t kd, double *dAB, int64_t ldab, int64_t strideAB, int32_t *d_info,
           int64_t batch, hipStream_t s) {
-    if (batch == 0) return BANDLU_OK;
     CholParams P;
-    P.AB = dAB;
-    P.info = d_info;
     P.ldab = ldab;
     P.strideAB = strideAB;
     P.n = (int)n;
     P.kd = (int)kd;
-    if (n > 0 && kd <= kCholTileMaxKd) return launch_pbtrf_tile(P, batch, s);
-    hipLaunchKernelGGL(pbtrf_global_kernel, dim3((unsigned)batch), dim3(kCholThreads), 0, s, P);
-    BANDLU_CHECK_LAUNCH("band_pbtrf");
+    // one workgroup per matrix, as many launches as their threads need
+    const int64_t chunk = max_groups(kCholTileThreads);
+    for (int64_t b0 = 0; b0 < batch; b0 += chunk) {
+        const int64_t count = std::min(chunk, batch - b0);
+        P.AB = dAB + b0 * strideAB;
+        P.info = d_info + b0;
+        if (chol_tile_fits(n, kd)) {
+            if (int rc = launch_pbtrf_tile(P, count, s); rc != BANDLU_OK) return rc;
+        } else {
+            hipLaunchKernelGGL(pbtrf_global_kernel, dim3((unsigned)count), dim3(kCholThreads), 0, s, P);
+            BANDLU_CHECK_LAUNCH("band_pbtrf");
+        }
+    }
     return BANDLU_OK;
 }
 

@@ -46,7 +46,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kB = 16;          // panel width and tile edge
 constexpr int kTile = kB * kB;  // doubles in a tile
-constexpr int kThreads = 512;
+constexpr int kThreads = kCholTileThreads;
 constexpr int kHelpers = 384;   // threads of the waves that work in phase 2 beside wave 0
 
 // sqrt(d) and 1/sqrt(d) for d in [2^-600, 2^600]: the operations of the

@@ -1,7 +1,8 @@
-// Band Cholesky in 16 x 16 tiles (kd <= kCholTileMaxKd).
+// Band Cholesky in 16 x 16 tiles (where chol_tile_fits()).
 #pragma once
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 
 namespace bandlu {
 
@@ -12,9 +13,7 @@ struct CholParams {
     int n, kd;
 };
 
-// the window's tiles fill LDS at 12 tile rows
-constexpr int kCholTileMaxKd = 144;
-
+// batch <= max_groups(kCholTileThreads)
 int launch_pbtrf_tile(const CholParams &P, int64_t batch, hipStream_t s);
 
 }  // namespace bandlu

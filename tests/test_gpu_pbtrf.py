@@ -78,3 +78,20 @@ def test_specials(kd):
     check(AB.copy(), kd, f"infinity kd={kd}")
     AB[20, 0] = np.inf
     check(AB, kd, f"infinite pivot kd={kd}")
+
+
+def test_more_systems_than_one_launch_holds():
+    """2^23 and a few systems of two rows: a launch of that many workgroups of
+    512 threads would be refused."""
+    batch = 2 ** 23 + 5
+    rng = np.random.default_rng(5000)
+    few = np.stack([lower(2, 1, 5000 + k) for k in range(97)])
+    few[5, 1, 0] = -1.0
+    pick = rng.integers(0, 97, batch)
+    ABg = gpu(few)[torch.from_numpy(pick).to("cuda")].contiguous()
+    print(f"pbtrf batch={batch}", flush=True)
+    info = bandlu.band_pbtrf_batched(ABg, 1)
+    torch.cuda.synchronize()
+    info_o = np.array([oracle.pbtrf(few[k], 1) for k in range(97)])
+    assert np.array_equal(info.cpu().numpy(), info_o[pick])
+    assert same(ABg.cpu().numpy(), few[pick])
