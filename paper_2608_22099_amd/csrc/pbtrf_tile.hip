@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kThreads, 2) void pbtrf_tile_kernel(CholParams P) {
         load();
         // (rows past kd are as they entered: a -0.0 there would not survive a
         // structurally zero multiplier)
-        const bool plain = nb == kB && __builtin_amdgcn_readfirstlane(*s_neg) < p + edge;
+        const bool plain = __builtin_amdgcn_readfirstlane(*s_neg) < p + edge;
         unsigned worst = 0;
         double g, r;  // the step's diagonal entry of L and its reciprocal (lane s)
         sqrt_recip(x[0][0], g, r);
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kThreads, 2) void pbtrf_tile_kernel(CholParams P) {
         const int c = kB * b + k / kB, i = kB * a + k % kB;
         const bool ok = i < n && c <= i && i - c <= kd;
         const double v = AB[ok ? (i - c) + int64_t(c) * ldab : 0];
-        if (b <= a) tile(0, a, b)[k] = ok ? v : 0.0;
+        if (b <= a) tile(0, a, b)[k] = ok ? v : (i == c && i >= n ? 1.0 : 0.0);
         if (ok && is_neg_zero(v)) atomicMax(s_neg, a);
     }
     // phase 2's pairs of tiles
@@ -377,8 +377,9 @@ __global__ __launch_bounds__(kThreads, 2) void pbtrf_tile_kernel(CholParams P) {
 #pragma unroll
                 for (int u = 0; u < T; ++u) {
                     const bool ok = entering(p, u);
+                    const bool past = u == T - 1 && ei == ec && kB * (p + 1 + T) + ei >= n;
                     neg |= ok && is_neg_zero(ent[u]);
-                    tile(pn, T, 1 + u)[ht] = ok ? ent[u] : 0.0;
+                    tile(pn, T, 1 + u)[ht] = ok ? ent[u] : (past ? 1.0 : 0.0);
                 }
                 if (neg) atomicMax(s_neg, p + 1 + T);
                 fetch(p + 1);

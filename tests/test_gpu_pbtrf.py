@@ -81,8 +81,8 @@ def test_specials(kd):
 
 
 def test_more_systems_than_one_launch_holds():
-    """2^23 and a few systems of two rows: a launch of that many workgroups of
-    512 threads would be refused."""
+    """2^23 and a few systems of two rows: of that many workgroups of 512 threads
+    one launch runs only the few, without an error."""
     batch = 2 ** 23 + 5
     rng = np.random.default_rng(5000)
     few = np.stack([lower(2, 1, 5000 + k) for k in range(97)])
