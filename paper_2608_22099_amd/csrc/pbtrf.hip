@@ -11,8 +11,9 @@
 //    A(i,c) -= L(i,j) L(c,j) to the trailing kd x kd triangle, one fused
 //    multiply-add per entry and step in the order of the steps, so the factor
 //    is bitwise that of the unblocked definition.  For kd <= 144 the window
-//    lives in LDS as 16 x 16 tiles (pbtrf_tile.hip); wider bands are updated
-//    in place in global memory, one column per barrier.
+//    lives in LDS as 16 x 16 tiles (pbtrf_tile.hip), for small systems (mostly
+//    batches of them) as columns, one per barrier; wider bands are
+//    updated in place in global memory, one column per barrier.
 //  * band_pbtrs: L y = b forward and L^T x = y backward, the dividing forward
 //    chain over L's columns and the backward chain over its rows.
 #include <algorithm>
@@ -28,6 +29,78 @@ int launch_chain(int mode, const RingParams &P, int64_t batch, hipStream_t s);
 namespace {
 
 constexpr int kCholThreads = 256;
+
+// Small systems (where chol_columns()): the columns j..j+kd+1 in LDS, kd+2 slots,
+// so that the column that enters is written while the step reads the others and
+// one barrier a step is enough.  Column c at slot c % (kd+2), entry r (row c+r) at
+// slot*(kd+1)+r.  Bound by the step's chain (0.3 us); eight workgroups a CU overlap.
+__global__ __launch_bounds__(kCholThreads) void pbtrf_column_kernel(CholParams P) {
+    extern __shared__ double win[];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = P.n, kd = P.kd, W = kd + 2, H = kd + 1;
+    double *AB = P.AB + int64_t(blockIdx.x) * P.strideAB;
+    const int64_t ldab = P.ldab;
+    auto at = [&](int c, int r) -> double & { return win[(c % W) * H + r]; };
+    // columns 0..kd enter
+    for (int q = tid; q < (kd + 1) * H; q += kCholThreads) {
+        const int c = q / H, r = q - c * H;
+        if (c < n) at(c, r) = c + r < n ? AB[r + int64_t(c) * ldab] : 0.0;
+    }
+    __syncthreads();
+    int info = 0;
+    // the columns that enter are read kPf steps ahead (a register ring), so
+    // that no step waits for its load
+    constexpr int kPf = 4;
+    auto ld_enter = [&](int ce) -> double {
+        return (ce < n && tid < H && ce + tid < n) ? AB[tid + int64_t(ce) * ldab] : 0.0;
+    };
+    double ring[kPf];
+#pragma unroll
+    for (int q = 0; q < kPf; ++q) ring[q] = ld_enter(kd + 1 + q);
+    for (int j0 = 0; j0 < n && !info; j0 += kPf)
+#pragma unroll
+    for (int q = 0; q < kPf; ++q) {
+        const int j = j0 + q;
+        if (j >= n) break;
+        const int kn = std::min(kd, n - 1 - j);
+        // the column that enters (j+kd+1), loaded kPf steps ago
+        const int ce = j + kd + 1;
+        const double enter = ring[q];
+        ring[q] = ld_enter(ce + kPf);
+        const double d0 = at(j, 0);
+        if (!(d0 > 0.0)) {
+            info = j + 1;
+            break;
+        }
+        const double d = __builtin_sqrt(d0);
+        const double r = 1.0 / d;
+        // trailing update A(j+b, j+a) for 1 <= a <= b <= kn: column j+a by
+        // wavefront, rows by lane (L(., j) formed where it is used)
+        const int sj = j % W;  // (one modulo per step; the other slots follow from it)
+        const double *cj = win + sj * H;
+        for (int a = 1 + wv; a <= kn; a += kCholThreads / 64) {
+            const int sa = sj + a >= W ? sj + a - W : sj + a;
+            double *ca = win + sa * H;
+            const double la = cj[a] * r;
+            for (int b = a + lane; b <= kn; b += 64)
+                ca[b - a] = __builtin_fma(-(cj[b] * r), la, ca[b - a]);
+        }
+        // column j is final
+        if (tid <= kn) AB[tid + int64_t(j) * ldab] = tid == 0 ? d : cj[tid] * r;
+        if (ce < n && tid < H) at(ce, tid) = enter;
+        __syncthreads();
+    }
+    if (info) {
+        // not positive definite at column info-1: the window's columns keep
+        // their updated values, as the unblocked algorithm leaves them
+        const int j = info - 1;
+        for (int q = tid; q < (kd + 1) * H; q += kCholThreads) {
+            const int c = j + q / H, r = q % H;
+            if (c < n && c + r < n && c <= j + kd) AB[r + int64_t(c) * ldab] = at(c, r);
+        }
+    }
+    if (tid == 0) P.info[blockIdx.x] = info;
+}
 
 __global__ __launch_bounds__(kCholThreads) void pbtrf_global_kernel(CholParams P) {
     const int tid = threadIdx.x;
@@ -84,7 +157,11 @@ int pbtrf(int64_t n, int64_t kd, double *dAB, int64_t ldab, int64_t strideAB, in
         const int64_t count = std::min(chunk, batch - b0);
         P.AB = dAB + b0 * strideAB;
         P.info = d_info + b0;
-        if (chol_tile_fits(n, kd)) {
+        if (n > 0 && chol_columns(n, kd, batch)) {
+            hipLaunchKernelGGL(pbtrf_column_kernel, dim3((unsigned)count), dim3(kCholThreads),
+                               size_t(kd + 2) * size_t(kd + 1) * sizeof(double), s, P);
+            BANDLU_CHECK_LAUNCH("band_pbtrf (columns)");
+        } else if (chol_tile_fits(n, kd)) {
             if (int rc = launch_pbtrf_tile(P, count, s); rc != BANDLU_OK) return rc;
         } else {
             hipLaunchKernelGGL(pbtrf_global_kernel, dim3((unsigned)count), dim3(kCholThreads), 0, s, P);

@@ -95,3 +95,34 @@ def test_more_systems_than_one_launch_holds():
     info_o = np.array([oracle.pbtrf(few[k], 1) for k in range(97)])
     assert np.array_equal(info.cpu().numpy(), info_o[pick])
     assert same(ABg.cpu().numpy(), few[pick])
+
+
+@pytest.mark.parametrize("n,kd,batch", [(1, 0, 3), (8, 7, 1), (9, 3, 512), (9, 3, 513), (12, 11, 1500),
+                                        (16, 1, 1100), (16, 4, 1100), (17, 16, 1024), (20, 4, 600),
+                                        (25, 4, 2048), (26, 4, 2048), (24, 12, 4096), (42, 4, 16384),
+                                        (43, 4, 16384), (109, 0, 16384), (50, 49, 2048), (56, 49, 2048),
+                                        (53, 52, 4096)])
+def test_small_systems(n, kd, batch):
+    """Both sides of the lines between the column kernel and the tiles: plain
+    systems, signed zeros, an infinity, scaled ones, and failing pivots."""
+    print(f"pbtrf n={n} kd={kd} batch={batch}", flush=True)
+    few = np.stack([lower(n, kd, 6000 + k, kd + 2) for k in range(13)])
+    inside = np.arange(n)[:, None] + np.arange(kd + 2) < n
+    inside[:, kd + 1] = False
+    pick = (np.random.default_rng(n).random((n, kd + 2)) < 0.5) & inside
+    pick[:, 0] = False
+    few[3, pick] = -0.0
+    few[5] = np.where(inside, np.ldexp(few[5], -900), few[5])
+    few[6, n - 1, 0] = -1.0
+    few[7, n // 2, 0] = np.nan
+    few[8, 0, 0] = 0.0
+    few[9, n // 3, 0] = np.inf
+    at = np.arange(batch) % 13
+    ABg = gpu(few)[torch.from_numpy(at).to("cuda")].contiguous()
+    info = bandlu.band_pbtrf_batched(ABg, kd)
+    torch.cuda.synchronize()
+    info_o = np.array([oracle.pbtrf(few[k], kd) for k in range(13)])
+    assert np.array_equal(info.cpu().numpy(), info_o[at])
+    ABg = ABg.cpu().numpy()
+    for k in range(min(13, batch)):
+        assert all(same(a, few[k]) for a in ABg[k::13])

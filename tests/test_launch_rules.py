@@ -38,3 +38,20 @@ def test_tiled_cholesky_row_numbers(tmp_path):
         assert fits or kd > 144 or n > 2 ** 31 - 1 - 224
         taken += fits
     assert taken > 0
+
+
+def test_small_cholesky_fits_lds(tmp_path):
+    """The column kernel's window (kd+2 columns of kd+1 entries, kd < n) stays
+    within the 64 KiB that need no attribute; beyond n = 8, few systems and
+    long ones keep the tiles."""
+    rows = run(tmp_path, """for (ll batch : {1LL, 512LL, 513LL, 1023LL, 1024LL, 2048LL, 4096LL, 16384LL, 1LL << 31})
+        for (ll n = 1; n <= 300; ++n)
+            for (ll kd = 0; kd < n && kd < 80; ++kd)
+                printf("%lld %lld %lld %d\\n", batch, n, kd, (int)chol_columns(n, kd, batch));""")
+    for batch, n, kd, col in rows:
+        assert not col or (kd + 2) * (kd + 1) * 8 <= 64 * 1024
+        if n <= 8:
+            assert col
+        elif batch <= 512 or n > 192:
+            assert not col
+    assert any(col and n > 8 for _, n, _, col in rows)
