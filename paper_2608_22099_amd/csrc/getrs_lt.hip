@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kLtThreads, 2) void lt_mfma_kernel(LtParams P, int 
     double *const ring = lds_lt;              // 2R doubles, then 64 that nobody reads
     double *const lbuf = lds_lt + 2 * R + 64; // two halves of NB rows, and room to read one row on
     const int nrow = n - 1;                   // rows n-2 .. 0
-    const int nhalf = (nrow + NB - 1) >> nbs;
+    const int nhalf = lt_halves(n, nbs);
 
     if (tid >= 64) {
         const double *__restrict__ AB = P.AB + b * P.strideAB;

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "launch_rules.hpp"
 
 namespace bandlu {
 

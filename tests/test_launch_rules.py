@@ -55,3 +55,11 @@ def test_small_cholesky_fits_lds(tmp_path):
         elif batch <= 512 or n > 192:
             assert not col
     assert any(col and n > 8 for _, n, _, col in rows)
+
+
+def test_halves_of_the_lt_pass(tmp_path):
+    """Every row of every accepted n (up to 2^31 - 1) is staged, in 32 bits."""
+    ns = list(range(2, 140)) + [2 ** 31 - 1 - d for d in range(70)]
+    body = "".join(f'printf("{n} {b} %d\\n", lt_halves({n}, {b}));\n' for n in ns for b in range(7))
+    for n, nbs, halves in run(tmp_path, body):
+        assert halves == -(-(n - 1) // 2 ** nbs)
