@@ -23,7 +23,10 @@
 // broadcast loads, 29.5 ms with this kernel (27 cycles per group of four where
 // the bare instruction chain takes 20, and about 400 cycles per row around
 // it).  Operands held 16 groups ahead instead of 8 ran at 24 cycles a group
-// and lost as much on padded rows.
+// and lost as much on padded rows.  Small systems are bound by what a workgroup
+// sets up: with the window, the halves and the loads cut to their size, 65536
+// systems (both passes) take 363 us for 390 at n = 8, kl = 1, and 1281 for 1363 at
+// n = 64, where the broadcast loads took 356 and 1304.
 #include <algorithm>
 
 #include "getrs_lt.hpp"
@@ -39,11 +42,15 @@ constexpr int kBlk = 4 * kGroups;       // terms to a block
 // multipliers in one half-buffer: 16 KiB, so that the whole workgroup stays
 // below 64 KiB of LDS (a half lasts wave 0 at least 5000 cycles, two trips to HBM)
 constexpr int kHalfMax = 2048;
+// multipliers that a loader brings to a half: all of the largest half, or those
+// of the smaller halves that many systems and few rows take
 constexpr int kPerLoader = (kHalfMax + kLtLoaders - 1) / kLtLoaders;
+constexpr int kPerLoaderSmall = 3;
 
-// TG: groups of a row's last block; MULTI: rows of more than one block.
+// TG: groups of a row's last block; MULTI: rows of more than one block; PL:
+// multipliers per loader.
 // kps: log2 of the multipliers kept per row; nbs: log2 of the rows per half
-template <int TG, bool MULTI>
+template <int TG, bool MULTI, int PL>
 __global__ __launch_bounds__(kLtThreads, 2) void lt_mfma_kernel(LtParams P, int kps, int nbs) {
     extern __shared__ double lds_lt[];
     const int tid = threadIdx.x;
@@ -61,9 +68,9 @@ __global__ __launch_bounds__(kLtThreads, 2) void lt_mfma_kernel(LtParams P, int 
         const int lt = tid - 64;
         auto stage = [&](int h) {
             double *dst = lbuf + (h & 1) * half;
-            double v[kPerLoader];
+            double v[PL];
 #pragma unroll
-            for (int i = 0; i < kPerLoader; ++i) {
+            for (int i = 0; i < PL; ++i) {
                 const int e = lt + kLtLoaders * i;
                 const int j = n - 2 - (h << nbs) - (e >> kps);
                 const int t = 1 + (e & ((1 << kps) - 1));
@@ -72,7 +79,7 @@ __global__ __launch_bounds__(kLtThreads, 2) void lt_mfma_kernel(LtParams P, int 
                 v[i] = ok ? -v[i] : -0.0;
             }
 #pragma unroll
-            for (int i = 0; i < kPerLoader; ++i) {
+            for (int i = 0; i < PL; ++i) {
                 const int e = lt + kLtLoaders * i;
                 if (e < half) dst[e] = v[i];
             }
@@ -211,14 +218,22 @@ __global__ __launch_bounds__(kLtThreads, 2) void lt_mfma_kernel(LtParams P, int 
     for (int q = lane; q < hi; q += 64) x[q] = ring[q & mask];
 }
 
+template <int TG, bool MULTI>
+void lt_launch(const LtParams &P, int64_t systems, size_t shm, int kps, int nbs, hipStream_t s) {
+    if ((1 << (nbs + kps)) <= kPerLoaderSmall * kLtLoaders)
+        hipLaunchKernelGGL((lt_mfma_kernel<TG, MULTI, kPerLoaderSmall>), dim3((unsigned)systems),
+                           dim3(kLtThreads), shm, s, P, kps, nbs);
+    else
+        hipLaunchKernelGGL((lt_mfma_kernel<TG, MULTI, kPerLoader>), dim3((unsigned)systems),
+                           dim3(kLtThreads), shm, s, P, kps, nbs);
+}
+
 template <int TG>
 void lt_launch(const LtParams &P, int64_t systems, size_t shm, int kps, int nbs, hipStream_t s) {
     if (P.kl > kBlk)
-        hipLaunchKernelGGL((lt_mfma_kernel<TG, true>), dim3((unsigned)systems), dim3(kLtThreads),
-                           shm, s, P, kps, nbs);
+        lt_launch<TG, true>(P, systems, shm, kps, nbs, s);
     else
-        hipLaunchKernelGGL((lt_mfma_kernel<TG, false>), dim3((unsigned)systems), dim3(kLtThreads),
-                           shm, s, P, kps, nbs);
+        lt_launch<TG, false>(P, systems, shm, kps, nbs, s);
 }
 
 }  // namespace
@@ -226,14 +241,17 @@ void lt_launch(const LtParams &P, int64_t systems, size_t shm, int kps, int nbs,
 int launch_getrs_lt(LtParams P, int64_t systems, hipStream_t s) {
     int kps = 5;
     while ((1 << kps) < P.kl) ++kps;
-    int R = 256;
-    while (R < P.kl + 192) R <<= 1;
+    // the window, or the whole vector and the kl positions past it (which have
+    // to be zero, not the slots of others)
+    int R = 64;
+    while (R < P.kl + std::min(P.n, 192)) R <<= 1;
     P.R = R;
     // rows per half: few where many systems share a CU (their LDS bounds how
-    // many fit), and less than the full half where the window is largest
+    // many fit), less than the full half where the window is largest, and no
+    // more than there are
     const int room = systems >= 512 ? 512 : (R > 1024 ? kHalfMax / 2 : kHalfMax);
     int nbs = 0;
-    while (nbs < 6 && (2 << (nbs + kps)) <= room) ++nbs;
+    while (nbs < 6 && (2 << (nbs + kps)) <= room && (1 << nbs) < P.n - 1) ++nbs;
     const size_t shm = (size_t(2) * R + 64 + (size_t(2) << (nbs + kps)) + (size_t(1) << kps) + kBlk) *
                        sizeof(double);
     // groups of the last block, rounded up to one of the compiled counts

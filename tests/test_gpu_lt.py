@@ -68,3 +68,24 @@ def test_lt_pass_infinity_and_many_systems():
     bandlu.band_getrs_t(gpu(AB), kl, ku, gpu(ipiv), Bg)
     torch.cuda.synchronize()
     assert same(Bg.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n,kl,ku", [(4, 3, 0), (5, 1, 0), (5, 4, 0), (33, 31, 1), (34, 33, 0), (60, 4, 0),
+                                     (61, 4, 0), (64, 1, 0), (100, 28, 0), (100, 29, 0), (128, 64, 0),
+                                     (160, 97, 0), (191, 65, 1), (192, 64, 1), (193, 63, 1), (200, 190, 0)])
+def test_lt_pass_small_windows(n, kl, ku):
+    """Vectors that fit the window whole: an infinity at each end and in between
+    meets no padded term (a zero times it would be NaN); one system and many."""
+    print(f"lt small n={n} kl={kl} ku={ku}", flush=True)
+    AB, ipiv, B = factors(n, kl, ku, 7200 + n, False)
+    at = [0, 1, n // 2, max(0, n - 1 - kl), n - 2, n - 1]
+    B = np.repeat(B[:1], 7, axis=0)
+    for r, q in enumerate(at):
+        B[r, q] = np.inf
+    ref = B.copy()
+    oracle.gbtrs_t(AB, kl, ku, ipiv, ref)
+    for copies in (1, 90):
+        Bg = gpu(np.tile(B, (copies, 1)))
+        bandlu.band_getrs_t(gpu(AB), kl, ku, gpu(ipiv), Bg)
+        torch.cuda.synchronize()
+        assert same(Bg.cpu().numpy(), np.tile(ref, (copies, 1)))
