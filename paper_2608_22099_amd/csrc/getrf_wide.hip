@@ -755,8 +755,10 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
                 asm volatile("" : "+v"(rcp0));
                 const int f = (hit & (hit - 1)) == 0 ? __builtin_ctzll(hit | (1ull << 63))
                                                      : settle(hit, (int)ylo, pos);
-                // (a wave with no candidate loses to every row)
-                if (lane == f) key[wvu] = make_int4((int)wmax, (int)ylo, hit == 0 ? INT_MAX : pos, 0);
+                // (a wave with no candidate loses to every row: its key is zero in
+                // both words, and its position comes last)
+                const bool none = hit == 0;
+                if (lane == f) key[wvu] = make_int4((int)wmax, none ? 0 : (int)ylo, none ? INT_MAX : pos, 0);
                 lds_barrier();
                 // the best of the waves' candidates: lane w of each group of
                 // eight looks at wave w's (places 5..7 never win)
