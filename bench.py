@@ -76,19 +76,34 @@ STEP_SOURCES = {
               "bufio.hpp", "common.hpp"],
 }
 # instantiation files of a step (one per parameter range), by name prefix
-STEP_PREFIXES = {"getrf": ("getrf_win_g", "getrf_lean_fwd", "getrf_split_c", "getrf_diag_ku"),
+STEP_PREFIXES = {"getrf": ("getrf_win_g", "getrf_lean_fwd", "getrf_split_", "getrf_diag_ku"),
                  "getrs": ("getrs_ring_fwd", "getrs_ring_bwd", "getrs_ring_div")}
+
+
+CSRC = os.path.join(ROOT, "paper_2608_22099_amd", "csrc")
+
+
+def step_files(step):
+    """The sources of one step.  A listed file or a prefix that no longer exists
+    is an error: a rename must not take a source out of the hash unseen."""
+    here = sorted(os.listdir(CSRC))
+    files = list(STEP_SOURCES[step])
+    missing = [f for f in files if f not in here]
+    for prefix in STEP_PREFIXES.get(step, ()):
+        found = [f for f in here if f.startswith(prefix) and f not in files]
+        files += found
+        if not found:
+            missing.append(prefix + "*")
+    if missing:
+        raise FileNotFoundError(f"sources of step {step}: no {', '.join(missing)} in csrc")
+    return files
 
 
 def source_hash(step):
     """sha256 over the sources of one step: its counters are valid only for these."""
     h = hashlib.sha256()
-    csrc = os.path.join(ROOT, "paper_2608_22099_amd", "csrc")
-    files = [f for f in STEP_SOURCES[step] if os.path.exists(os.path.join(csrc, f))]
-    for prefix in STEP_PREFIXES.get(step, ()):
-        files += sorted(f for f in os.listdir(csrc) if f.startswith(prefix))
-    for f in files:
-        with open(os.path.join(csrc, f), "rb") as fh:
+    for f in step_files(step):
+        with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(f.encode() + b"\0" + fh.read())
     return h.hexdigest()
 
