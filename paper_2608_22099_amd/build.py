@@ -69,9 +69,10 @@ def _compile(src, incremental=False, hdr_mtime=0.0):
     # Every kernel must run without scratch memory: a register array indexed
     # at run time or a spill would fall back to it, which is slow, and a large
     # per-lane scratch size makes the runtime reserve memory for every wave slot.
-    # The persistent wide-band kernel is the one exception, with a bound: a
-    # few registers of its column steps spill (its launch has at most one
-    # workgroup per CU, so the reserve is small).
+    # The persistent wide-band kernel is the one exception, with a bound: at
+    # 256 registers a lane about 50 of its values spill, most of them around
+    # the trailing update (see the substitution's figures there).  Its launch
+    # has at most one workgroup per CU, so the reserve is small.
     fn, bad = None, []
     for line in r.stderr.splitlines():
         m = re.search(r"Function Name: (\S+)", line)

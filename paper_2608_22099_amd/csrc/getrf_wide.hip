@@ -357,9 +357,11 @@ __global__ __launch_bounds__(kThreads) void getrf_wide_kernel(WideParams P) {
                 // the matrix cores (in the order of the steps, as below): a step by
                 // lanes reads its factors from LDS at about 20 cycles each, so the
                 // 256 that the product takes over are half of the substitution.
-                // Measured (dominant rows): n = 32768, kl = ku = 256 27.48 -> 27.10
-                // ms, n = 10000, kl = ku = 100 8.31 -> 8.10, though 184 more bytes
-                // a lane spill around the update below.
+                // Measured, dominant rows: n = 32768, kl = ku = 256 27.53 -> 27.15 ms,
+                // n = 10000, kl = ku = 100 8.33 -> 8.18, other single matrices 1-2 %
+                // less.  184 more bytes a lane spill around the update below; batches
+                // whose panels interchange take 2-6 % more for it (16 systems of n =
+                // 1000, kl = 200, ku = 256: 1.81 -> 1.92 ms), single ones do not.
                 // rows j0..j0+31 are 32 consecutive physical rows (288 and
                 // every window start are multiples of 32)
                 double *const top = W + opaque(prow(j0) * LDW);

@@ -1,6 +1,6 @@
 // Band Cholesky for kd <= 144: panels of 16 columns, the trailing triangle on
 // the matrix cores (the Cholesky case the paper names beside LU, end of
-// Sec. II-B).
+// Sec. II-B).  (Batches of small systems go by columns: chol_columns().)
 //
 // What bounds it is the chain of n column steps (update of the next diagonal
 // entry, square root, reciprocal, scaling), not the n*kd^2 operations.  One
@@ -49,9 +49,10 @@ constexpr int kTile = kB * kB;  // doubles in a tile
 constexpr int kThreads = kCholTileThreads;
 constexpr int kHelpers = 384;   // threads of the waves that work in phase 2 beside wave 0
 
-// sqrt(d) and 1/sqrt(d) for d in [2^-600, 2^600]: the operations of the
-// library's square root and of the hardware's division sequence without their
-// scaling steps, which such values do not need (so the results are theirs).
+// sqrt(d) and 1/sqrt(d) for d in [2^-600, 2^600]: Goldschmidt's iteration from
+// the hardware's estimate, then corrections by the exact residual (fma) until the
+// root and the quotient are correctly rounded, as sqrt and 1/x are; such values
+// need no scaling.
 __device__ __forceinline__ void sqrt_recip(double d, double &g, double &r) {
     const double y = __builtin_amdgcn_rsq(d);
     const double s0 = d * y, h0 = y * 0.5;

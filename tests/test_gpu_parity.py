@@ -187,7 +187,7 @@ def test_getrf_window_boundaries(kl, ku):
         assert_bitwise(g[1], o[1], f"n={n} kl={kl} ku={ku}")
 
 
-# The two-wavefront kernel and the one-wavefront window run the same
+# The pivot-wavefront kernel and the one-wavefront window run the same
 # operations: both must reproduce the oracle bit for bit, with and without
 # row interchanges (no diagonal shift: interchanges at most steps).
 SPLIT_SHAPES = [(2, 1, 0), (2, 1, 1), (3, 2, 0), (40, 1, 0), (50, 3, 2), (300, 3, 3), (300, 16, 16),
@@ -210,7 +210,7 @@ def test_getrf_split_exact(n, kl, ku):
 
 def test_getrf_split_special():
     """Singular columns, NaN entries, pivots below DBL_MIN and a zero matrix
-    through the two-wavefront kernel."""
+    through the pivot-wavefront kernel."""
     n, kl, ku = 60, 3, 2
     cases = []
     for k in (0, 7, 59):
@@ -342,7 +342,7 @@ def test_lean_window_random(seed):
 
 # The diagonal-pivot kernel must give the oracle's factors bit for bit
 # whether every column keeps its diagonal pivot (dominant bands), a column
-# fails the check (the two-wavefront kernel takes over there) or the first
+# fails the check (the pivot-wavefront kernel takes over there) or the first
 # one does (no diagonal shift: interchanges at most steps).
 DIAG_SHAPES = [(2, 1, 1), (3, 1, 1), (40, 1, 1), (300, 16, 16), (1000, 3, 3), (257, 1, 2),
                (129, 5, 8), (200, 11, 20), (97, 18, 16), (70, 1, 24), (64, 2, 9), (66, 7, 13),
@@ -383,7 +383,7 @@ def test_getrf_diag_exact(n, kl, ku):
 def test_getrf_diag_resume(n, kl, ku, cols):
     """A dominant band with one weak diagonal: the diagonal-pivot kernel stops
     at that column (the last one has no candidates and never stops) and the
-    two-wavefront kernel factors the rest."""
+    pivot-wavefront kernel factors the rest."""
     for col in cols:
         T = dominant_band(n, kl, ku, 900 + col)
         T[col, col] = 1e-3  # T[j, i] is A[i, j]

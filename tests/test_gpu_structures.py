@@ -8,8 +8,8 @@ for bit (every kernel here performs the oracle's operations in its order):
 * the fused detect-and-convert pass.
 
 Shapes span the kernels' internal limits: ring register groups (K > 63), the
-any-band kernel (K > 1023), the L^T pass's window chunks (kl > 64), the
-Cholesky LDS window (kd <= 140) and its global-memory form, ragged sizes,
+any-band kernel (K > 1023), the L^T pass's blocks of terms (kl > 32), the
+Cholesky's tiles (kd <= 144) and its global-memory form, ragged sizes,
 batches, empty inputs and the degenerate cases (zero diagonal, not positive
 definite, exceeded caps)."""
 import numpy as np
