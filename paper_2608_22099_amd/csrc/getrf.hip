@@ -54,17 +54,17 @@ WinKernel win_kernel_g16_c2_h1_8(int H);
 WinKernel split_kernel_h2_16(int H);
 WinKernel split_kernel_h17_24(int H);
 WinKernel split_kernel_h25_32(int H);
-WinKernel split_one_h2_16(int H);
+WinKernel split_one_h8_16(int H);
 WinKernel split_one_h17_24(int H);
 WinKernel split_one_h25_32(int H);
 WinKernel split_two_h8_16(int H);
 WinKernel lean64_fwd_kernel_c1(int H);
 WinKernel lean64_fwd_kernel_c2(int H);
 
-// pivot-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32: one update
-// wavefront, or any number
+// pivot-wavefront kernel (getrf_split.hpp) for 2 <= H <= 32: any number of update
+// wavefronts, or one (H >= 8: below that the two take the same time)
 WinKernel split_kernel(int H, bool one) {
-    if (H <= 16) return one ? split_one_h2_16(H) : split_kernel_h2_16(H);
+    if (H <= 16) return one ? split_one_h8_16(H) : split_kernel_h2_16(H);
     if (H <= 24) return one ? split_one_h17_24(H) : split_kernel_h17_24(H);
     return one ? split_one_h25_32(H) : split_kernel_h25_32(H);
 }
@@ -297,7 +297,7 @@ int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int6
     W.resume = 0;
     const int64_t need = 2 * kl + ku + 1;
     const bool two = split_two_columns(kl, need, batch);
-    const WinKernel k = two ? split_two_h8_16((int)kl + 1) : split_kernel((int)kl + 1, need <= 64);
+    const WinKernel k = two ? split_two_h8_16((int)kl + 1) : split_kernel((int)kl + 1, need <= 64 && kl >= 7);
     if (!k) {
         set_error("band_getrf: no pivot-wavefront kernel for kl = %lld", (long long)kl);
         return BANDLU_ERR_UNSUPPORTED;

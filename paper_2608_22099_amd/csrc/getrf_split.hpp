@@ -99,7 +99,7 @@ __device__ __forceinline__ void split_swap(double (&a)[H], int p) {
 }
 
 // CPL: columns per lane; NU: waves U (0: as many as the launch has).  One wave U
-// has kernels of its own: with M known, single matrices of kl = 9..31 took 2-12 %
+// has kernels of its own from kl = 7 on: with M known, single matrices of kl = 9..31 took 2-12 %
 // less (kl = 16, n = 5000: 3525 -> 3305 us random, 2930 -> 2645 dominant).
 // CPL = 2 (one wave U for 65..128 columns) runs batches whose matrices all fit
 // the chip at once: see split_two_columns() in getrf.hip.
@@ -366,7 +366,7 @@ struct SplitRange {
 WinKernel split_kernel_h2_16(int H);
 WinKernel split_kernel_h17_24(int H);
 WinKernel split_kernel_h25_32(int H);
-WinKernel split_one_h2_16(int H);
+WinKernel split_one_h8_16(int H);
 WinKernel split_one_h17_24(int H);
 WinKernel split_one_h25_32(int H);
 WinKernel split_two_h8_16(int H);
