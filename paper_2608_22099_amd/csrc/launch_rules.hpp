@@ -49,6 +49,6 @@ constexpr bool chol_columns(int64_t n, int64_t kd, int64_t batch) {
 
 // L^T pass (getrs_lt.hip): halves of 2^nbs rows that stage rows n-2 .. 0, n >= 2
 // (both sides of the kernel count their barriers by it).
-constexpr int lt_halves(int n, int nbs) { return ((n - 2) >> nbs) + 1; }
+constexpr int lt_halves(int n, int nbs) { return int((unsigned(n - 1) + (1u << nbs) - 1) >> nbs); }
 
 }  // namespace bandlu
