@@ -257,12 +257,16 @@ bool split_fits(int64_t n, int64_t kl, int64_t ku, int64_t ldab, int64_t batch) 
 // 270; kl = 10: 249 for 352), barely above two otherwise (640 systems, 100
 // columns, kl = 10: 217 for 239).  For kl = 13 and 14 the two wavefronts' registers
 // leave room for two matrices per CU only (4096 systems, 65 columns, kl = 14: 1214
-// us for 1664); from about 80 columns on that is no loss (100 columns: 2041 for
-// 1725), as fewer matrices share the cache.
+// us for 1664; 768 systems, 90 columns: 328 for 388); from about 80 columns on that
+// is no loss beyond three per CU (100 columns, 4096 systems: 2041 for 1725), as
+// fewer matrices share the cache.  kl = 15 has four per CU either way (1024 systems:
+// 65 columns 285 us for 272, 80 columns 346 for 403; 640 systems, 100 columns: 267
+// for 262).
 bool split_two_columns(int64_t kl, int64_t need, int64_t batch) {
     if (need <= 64 || need > 128 || kl < 7 || kl > 15 || batch <= 512) return false;
-    if (need > 80) return batch <= 704;
-    return batch <= 1024 || kl == 13 || kl == 14;
+    const bool wide = kl == 13 || kl == 14;
+    if (need > 80) return kl < 15 && batch <= (wide ? 768 : 704);
+    return wide || batch <= 1024;
 }
 
 // Dynamic LDS that keeps a fifth workgroup off a CU.  A step touches one line per
@@ -271,12 +275,16 @@ bool split_two_columns(int64_t kl, int64_t need, int64_t batch) {
 // more be resident, large batches are faster with four (8192 systems of n = 256,
 // kl = 9, 80 columns: 2634 us for 3118, 2807 with two columns per lane; of n =
 // 200, kl = 16, 64 columns, dominant: 1265 for 1488).  One wavefront U and at most
-// 56 columns: all that fit (kl = 16, 40 columns: 1044 us for 1386).
-unsigned split_lds(int64_t kl, int64_t need, int64_t batch) {
+// 56 columns: all that fit (kl = 16, 40 columns: 1044 us for 1386).  Batches of a
+// single round, and matrices of few steps, are faster with all that fit too (time
+// with four over that without: kl = 16, 64 columns, 8192 systems: 1.31 at n = 40,
+// 1.08 at 128, 0.99 at 160, 0.92 at 256; kl = 9, 80 columns: 1.13 at 64, 1.00 at
+// 96, 0.89 at 128; 1100 systems: 1.2-1.4).
+unsigned split_lds(int64_t steps, int64_t kl, int64_t need, int64_t batch) {
     constexpr unsigned four = 38000;  // (each kernel has 1552 bytes of its own)
-    if (batch <= 1024 || need > 128) return 0;
-    if (need > 64) return four;
-    return need > 56 && kl >= 16 && kl <= 19 ? four : 0;
+    if (batch < 2048 || need > 128) return 0;
+    if (need > 64) return steps >= 96 ? four : 0;
+    return need > 56 && kl >= 16 && kl <= 19 && steps >= 160 ? four : 0;
 }
 
 int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int64_t ldab,
@@ -303,7 +311,7 @@ int launch_split(int64_t m, int64_t n, int64_t kl, int64_t ku, double *dAB, int6
         return BANDLU_ERR_UNSUPPORTED;
     }
     hipLaunchKernelGGL(k, dim3((unsigned)batch), dim3(two ? 128 : split_threads(kl, ku)),
-                       two ? 0 : split_lds(kl, need, batch), s, W);
+                       two ? 0 : split_lds(std::min(m, n), kl, need, batch), s, W);
     BANDLU_CHECK_LAUNCH("band_getrf (pivot wavefront)");
     return BANDLU_OK;
 }

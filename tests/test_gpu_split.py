@@ -103,15 +103,16 @@ def test_batched():
 
 
 @pytest.mark.parametrize("batch,kl,need", [(513, 7, 65), (1024, 12, 80), (1030, 14, 66), (1025, 13, 80),
-                                           (704, 15, 81), (600, 9, 128), (705, 11, 81), (1025, 9, 65),
-                                           (1025, 15, 128), (1025, 16, 57), (1030, 19, 64)])
+                                           (704, 15, 81), (600, 9, 128), (705, 11, 81), (768, 14, 90),
+                                           (2048, 9, 65), (2048, 15, 73), (1024, 15, 65), (2050, 7, 128),
+                                           (2048, 16, 57), (2049, 19, 64)])
 def test_batch_rules(batch, kl, need):
     """Batches at the edges of the rules for two columns per lane and for the
     number of resident workgroups; a few matrices of each batch, and the same
     for a band of fewer rows than columns."""
     ku = need - 2 * kl - 1
     print(f"batch={batch} kl={kl} need={need}", flush=True)
-    for m, n in ((need + 70, need + 70), (need + 40, need + 70)):
+    for m, n in ((need + 140, need + 140), (need + 100, need + 140)):
         base = [band(m, n, kl, ku, 1300 + b, b % 2 * 2.0 * (kl + ku)) for b in range(5)]
         AB = np.stack([base[b % 5] for b in range(batch)])
         ABg = gpu(AB)
