@@ -20,7 +20,7 @@
 // positions a row reads are consecutive.
 //
 // Measured, n = 32768, kl = ku = 256, one right-hand side: 88.5 ms with the
-// broadcast loads, 29.5 ms with this kernel (27 cycles per group of four where
+// broadcast loads, 28.9 ms with this kernel (26 cycles per group of four where
 // the bare instruction chain takes 20, and about 400 cycles per row around
 // it).  Operands held 16 groups ahead instead of 8 ran at 24 cycles a group
 // and lost as much on padded rows.  Small systems are bound by what a workgroup
